@@ -22,7 +22,7 @@ TAU_BASE, TAU_RESCUE = 0.9, 0.95  # the thresholds of the repository's workloads
 N_SINK, N_LOCAL, N_RECENT = 1, 2, 0
 BOX_BUDGET = 0.1                  # budget fraction of the Quest-style selector
 #: Work of the largest listed case (in executed query-key pairs times heads): what a drawn one may cost.
-MOST_PAIRS = 0.22 * 32 * 131072**2 / 2
+MOST_PAIRS = 0.29 * 32 * 131072**2 / 2
 #: exact() stops here (heads times tokens squared): the 64-bit attention of a larger case takes too long.
 MOST_EXACT = 1.1 * 64 * 65536**2
 
@@ -248,8 +248,8 @@ def _density(kind, n, b, dense):
         return min(0.9, 0.07 * (131072 / n) ** 0.85)
     if kind == "variant":
         return BOX_BUDGET
-    at_128k = {64: 0.013, 128: 0.22, 256: 0.73}[b]
-    return min(1.0, at_128k ** (1.0 - min(1.0, math.log2(max(1.0, 131072 / n)) / 6.0)))
+    at_128k, halvings = {64: (0.018, 6.5), 128: (0.29, 3.5), 256: (0.75, 3.5)}[b]
+    return at_128k ** (1.0 - min(1.0, math.log2(max(1.0, 131072 / n)) / halvings))
 
 
 def work(case):

@@ -513,33 +513,40 @@ __device__ __forceinline__ void work_item(int M, int group, int& h, int& i) {
 // tail of the slower ones.  kQueueInts int32 counters, zeroed by reset_queues
 // before each launch.
 
-// Cursor of a workgroup over the queues: the queue it takes tickets from and
-// the number of queues it has not yet found empty.
-struct QueueCursor {
-  int q, left;
-};
-
-__device__ __forceinline__ QueueCursor first_queue() { return {(int)(blockIdx.x & (kQueues - 1)), kQueues}; }
+// The queue a workgroup takes its first tickets from.
+__device__ __forceinline__ int first_queue() { return (int)(blockIdx.x & (kQueues - 1)); }
 
 // The next work slot (< total) for this workgroup, the same value in every
 // thread, or -1 once every queue is empty.  Wave 0 takes a ticket (one
 // increment, made by its lane 0; the other lanes add zero) and passes it
 // through LDS; the barrier makes it visible and is also the one every wave
 // passes before the tiles of the previous item may be overwritten.  A ticket
-// past the end of its queue means the queue is empty (tickets only grow).
-// Control flow stays uniform throughout: no lane-divergent branch surrounds a
-// barrier.
-__device__ __forceinline__ int next_slot(int* queue, int total, int* lds_slot, QueueCursor& cur) {
+// past the end of its queue means the queue is empty (tickets only grow); the
+// wave then looks at all eight counters at once (lane l reads counter l % 8)
+// and goes on to the next queue with a slot left, so that the end of a launch
+// costs a workgroup two round trips and not one per queue (700 dense tokens, 32
+// heads, B = 128: 44.6 -> 25.7 us; 2048 tokens, 2 heads, B = 64: 67.4 -> 49.0
+// us).  Control flow around the barriers is uniform.
+__device__ __forceinline__ int next_slot(int* queue, int total, int* lds_slot, int& q) {
   for (;;) {
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
-      const int t = atomicAdd(queue + cur.q, (threadIdx.x & 63) == 0 ? 1 : 0);
-      *lds_slot = __builtin_amdgcn_readfirstlane(t);
+      const int lane = threadIdx.x & 63;
+      const int t = __builtin_amdgcn_readfirstlane(atomicAdd(queue + q, lane == 0 ? 1 : 0));
+      int next = kQueues * t + q;
+      if (next >= total) {
+        const int l = lane & (kQueues - 1);
+        const int c = __hip_atomic_load(queue + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t open = (uint32_t)__ballot(kQueues * c + l < total) & ((1u << kQueues) - 1);
+        // -1: every queue is empty; -2 - p: queue p is the next one to try.
+        const uint32_t ring = open | (open << kQueues);  // queues q + 1 .. q + 8, cyclically
+        next = open == 0 ? -1 : -2 - ((q + __builtin_ctz(ring >> (q + 1)) + 1) & (kQueues - 1));
+      }
+      *lds_slot = next;
     }
     __syncthreads();
-    const int slot = kQueues * __builtin_amdgcn_readfirstlane(*lds_slot) + cur.q;
-    if (slot < total) return slot;
-    if (--cur.left == 0) return -1;
-    cur.q = (cur.q + 1) & (kQueues - 1);
+    const int slot = __builtin_amdgcn_readfirstlane(*lds_slot);
+    if (slot >= -1) return slot;
+    q = -2 - slot;
     __syncthreads();  // every wave has read lds_slot before wave 0 writes the next ticket
   }
 }

@@ -38,9 +38,9 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ __align__(1024) unsigned char k_lds[BS * 256];
   __shared__ __align__(1024) unsigned char v_lds[BS * 256];
   __shared__ int lds_slot;
-  QueueCursor cur = first_queue();
+  int q = first_queue();
   for (;;) {
-    const int slot = next_slot(queue, total, &lds_slot, cur);
+    const int slot = next_slot(queue, total, &lds_slot, q);
     if (slot < 0) break;
     attend_slot<BS>(c, counts, indices, capacity, slot, total, k_lds, v_lds);
     __syncthreads();  // tiles and lds_slot free for the next item
@@ -91,9 +91,9 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ __align__(1024) unsigned char k_lds[BS * 256];
   __shared__ __align__(1024) unsigned char v_lds[BS * 256];
   __shared__ int lds_slot;
-  QueueCursor cur = first_queue();
+  int q = first_queue();
   for (;;) {
-    const int slot = next_slot(queue, total, &lds_slot, cur);
+    const int slot = next_slot(queue, total, &lds_slot, q);
     if (slot < 0) break;
     attend_slot_varlen<BS>(c, counts, indices, t, slot, total, k_lds, v_lds);
     __syncthreads();

@@ -415,9 +415,9 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
   __shared__ int lds_slot;
   const int total = c.M * c.Hq;
-  QueueCursor cur = first_queue();
+  int q = first_queue();
   for (;;) {
-    const int slot = next_slot(queue, total, &lds_slot, cur);
+    const int slot = next_slot(queue, total, &lds_slot, q);
     if (slot < 0) break;
     int h, i;
     work_of(slot, total, c.M, c.Hq / c.Hkv, h, i);

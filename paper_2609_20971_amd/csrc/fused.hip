@@ -45,9 +45,9 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ int lds_slot;
   typedef __attribute__((address_space(3))) int32_t lds_i32;
   lds_i32* list_lds = (lds_i32*)(smem + fused_region_bytes<BS>(ac.M));
-  QueueCursor cur = first_queue();
+  int q = first_queue();
   for (;;) {
-    const int slot = next_slot(queue, total, &lds_slot, cur);
+    const int slot = next_slot(queue, total, &lds_slot, q);
     if (slot < 0) break;
     int h, i;
     work_of(slot, total, ac.M, ac.group, h, i);

@@ -73,6 +73,19 @@ def test_queue_with_fewer_items_than_queues():
                  "2 items")
 
 
+@pytest.mark.parametrize("heads,blocks", [(1, 1), (1, 7), (1, 8), (3, 3), (1, 17), (8, 8), (1, 65)])
+def test_queue_item_counts_around_the_queue_count(heads, blocks):
+    """1 to 65 items over the 8 queues: empty queues, queues of unequal length
+    and a last ticket in each, where a workgroup goes from queue to queue and
+    has to stop once all are empty."""
+    w = WORKLOADS["tiny-2k"].with_(name="queue-count", seq_len=64 * blocks - 5, n_q_heads=heads, n_kv_heads=1,
+                                   block_size=64, needles_per_kv_head=0, seed=50 + blocks)
+    _say(f"[queue] {heads * blocks} items")
+    shape, Q, K, V, counts, indices = _setup(w, dense=True)
+    _assert_same(_attend(shape, Q, K, V, counts, indices, None), _attend(shape, Q, K, V, counts, indices, "auto"),
+                 f"{heads * blocks} items")
+
+
 def test_caller_workspace_with_stale_contents_and_reuse():
     """A caller's workspace holding arbitrary values is reset by the call; the
     same workspace then serves a second, smaller problem."""

@@ -1062,8 +1062,6 @@ KERNEL_SOURCES = {
     "quantile_kernel": ["stats.hip", "rbs_device.hpp", "../build.py"],
     "select_kernel": ["select.hip", "select_block.hpp", "rbs_device.hpp", "../build.py"],
     "attn_queue_kernel": ["attn.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
-    "select_attend_queue_kernel": ["fused.hip", "select_block.hpp", "attend_block.hpp", "rbs_device.hpp",
-                                   "rbs_launch.hpp", "../build.py"],
     "attn_fp8_queue_kernel": ["fp8.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
 }
 

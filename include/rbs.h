@@ -9,7 +9,7 @@
  *                       query-block key-block index lists     (Sec. 3.2)
  *   rbs_sparse_prefill  causal GQA block-sparse attention over the selected
  *                       blocks                                (Sec. 3.3)
- *   rbs_select_attend   both in one pass (Algorithm 1 from the selection loop
+ *   rbs_select_attend   both in one call (Algorithm 1 from the selection loop
  *                       on), same results as the two calls in sequence
  *   rbs_block_box,      the supporting selectors of the paper's selector
  *   rbs_select_variant  comparison (centroid-only, full-L2 bound, Quest-style
@@ -222,15 +222,11 @@ int rbs_sparse_prefill_noalloc(const rbs_shape* shape, const void* Q, const void
                                const int32_t* counts, const int32_t* indices, float softmax_scale, void* O,
                                float* lse, void* stream);
 
-/* rbs_select then rbs_sparse_prefill in one pass (Algorithm 1, selection loop
- * and attention; Sec. 3.2-3.3): each (query head, query block) selects its key
- * blocks and attends over them at once, the list kept on chip.  Arguments as
- * in the two calls; counts/indices are still written (same layout and values
- * as rbs_select), and O/lse equal those of rbs_sparse_prefill on those lists.
- * Saves the second read of Q and the round trip of the lists through memory.
- * The persistent launch (workspace non-NULL) is taken at B = 128 only; at
- * B = 64 and 256 the call runs one workgroup per item and leaves the
- * workspace unused.
+/* rbs_select then rbs_sparse_prefill in one call (Algorithm 1, selection loop
+ * and attention; Sec. 3.2-3.3): the two stages' kernels, one after the other
+ * on `stream`.  Arguments as in the two calls; counts/indices are written (same
+ * layout and values as rbs_select), and O/lse equal those of
+ * rbs_sparse_prefill on those lists.
  * Validation and errors: the union of the two calls' rules.
  */
 int rbs_select_attend(const rbs_shape* shape, const void* Q, const void* K, const void* V,

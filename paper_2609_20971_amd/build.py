@@ -15,7 +15,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "librbs.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["api.hip", "stats.hip", "select.hip", "attn.hip", "fused.hip", "fp8.hip"]
+SOURCES = ["api.hip", "stats.hip", "select.hip", "attn.hip", "fp8.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -38,11 +38,11 @@ FLAGS = [
 # The attention kernels use the iterative ILP machine scheduler: the default
 # one issued every K-tile LDS read right before the matrix op that consumes
 # it and waited for it there (32 serialized read-wait-MFMA steps per block);
-# the ILP schedule keeps several reads in flight (attention 3-4% faster, the
-# fused selection + attention kernel 3%).  The FP8 attention kernel keeps the
-# default scheduler: the ILP one made it 1.5x slower.
+# the ILP schedule keeps several reads in flight (attention 3-4% faster).  The
+# FP8 attention kernel keeps the default scheduler: the ILP one made it 1.5x
+# slower.
 _ILP = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
-EXTRA_FLAGS = {"select.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "attn.hip": _ILP, "fused.hip": _ILP}
+EXTRA_FLAGS = {"select.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "attn.hip": _ILP}
 
 
 def _run(cmd):

@@ -393,7 +393,12 @@ int rbs_select_attend(const rbs_shape* shape, const void* Q, const void* K, cons
   aa.queue = static_cast<int*>(workspace);
   rc = check_q_range(Q, st.q_head, st.q_tok, shape->n_q_heads, shape->n_tokens, stream);
   if (rc != RBS_OK) return rc;
-  return finish(rbs::launch_select_attend(sa, aa, static_cast<hipStream_t>(stream)), stream);
+  // The two stages' own kernels, one after the other: a kernel that did both
+  // kept its selection at the attention's occupancy (2 workgroups per compute
+  // unit) and was slower at every block size.
+  hipError_t e = rbs::launch_select(sa, static_cast<hipStream_t>(stream));
+  if (e == hipSuccess) e = rbs::launch_attention(aa, static_cast<hipStream_t>(stream));
+  return finish(e, stream);
 }
 
 size_t rbs_box_summary_bytes(const rbs_shape* shape) {

@@ -142,7 +142,9 @@ int64_t rbs_index_capacity(int32_t n_blocks);
  *             the same order as with NULL, so results are bit-identical; the
  *             launch avoids the idle workgroup slots that in-order dispatch of
  *             rows of very different lengths leaves (a sparse selection's
- *             rows differ by an order of magnitude).
+ *             rows differ by an order of magnitude).  A call with no more
+ *             items than that runs them all at once, one workgroup each, and
+ *             leaves the workspace alone.
  * The call resets the queues itself (with a kernel on `stream`, no memset):
  * contents on entry are ignored and undefined afterwards.  The workspace is
  * written by the call like an output, so calls that share one must be

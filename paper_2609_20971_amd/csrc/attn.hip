@@ -151,31 +151,28 @@ __global__ void dense_indices_kernel(int M, int64_t capacity, int32_t* __restric
   if (threadIdx.x == 0) counts[(size_t)h * M + i] = i + 1;
 }
 
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
+template <int BS>
+static hipError_t launch_attention_bs(const AttnCore& c, const AttnArgs& a, hipStream_t s) {
   const int total = a.n_blocks * a.n_q_heads;
+  return launch_slots<attn_queue_kernel<BS>>(
+      BS * 2, total, a.queue, s,
+      [&](int grid) {
+        hipLaunchKernelGGL(attn_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, a.capacity);
+      },
+      [&](int grid) {
+        hipLaunchKernelGGL(attn_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, a.capacity,
+                           total, a.queue);
+      });
+}
+
+hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   const AttnCore c = make_attn_core(a);
-  int grid = 0;
-#define RBS_ATTN_CASE(BSZ)                                                                                     \
-  case BSZ:                                                                                                    \
-    if (a.queue == nullptr) {                                                                                  \
-      hipLaunchKernelGGL(attn_kernel<BSZ>, dim3(total), dim3(BSZ * 2), 0, s, c, a.counts, a.indices,          \
-                         a.capacity);                                                                          \
-    } else {                                                                                                   \
-      hipError_t e = resident_grid<attn_queue_kernel<BSZ>>(BSZ * 2, total, &grid);                             \
-      if (e == hipSuccess) e = reset_queues(a.queue, s);                                                       \
-      if (e != hipSuccess) return e;                                                                           \
-      hipLaunchKernelGGL(attn_queue_kernel<BSZ>, dim3(grid), dim3(BSZ * 2), 0, s, c, a.counts, a.indices,     \
-                         a.capacity, total, a.queue);                                                          \
-    }                                                                                                          \
-    break;
   switch (a.block_size) {
-    RBS_ATTN_CASE(64)
-    RBS_ATTN_CASE(128)
-    RBS_ATTN_CASE(256)
+    case 64: return launch_attention_bs<64>(c, a, s);
+    case 128: return launch_attention_bs<128>(c, a, s);
+    case 256: return launch_attention_bs<256>(c, a, s);
     default: return hipErrorInvalidValue;
   }
-#undef RBS_ATTN_CASE
-  return hipGetLastError();
 }
 
 __global__ void dense_indices_varlen_kernel(const SeqTable t, int32_t* __restrict__ counts,
@@ -188,30 +185,28 @@ __global__ void dense_indices_varlen_kernel(const SeqTable t, int32_t* __restric
   if (threadIdx.x == 0) counts[(size_t)h * t.blk[t.n] + bg] = i + 1;
 }
 
-hipError_t launch_attention_varlen(const AttnArgs& a, const SeqTable& t, hipStream_t s) {
+template <int BS>
+static hipError_t launch_attention_varlen_bs(const AttnCore& c, const AttnArgs& a, const SeqTable& t, hipStream_t s) {
   const int total = t.blk[t.n] * a.n_q_heads;
+  return launch_slots<attn_varlen_queue_kernel<BS>>(
+      BS * 2, total, a.queue, s,
+      [&](int grid) {
+        hipLaunchKernelGGL(attn_varlen_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, t);
+      },
+      [&](int grid) {
+        hipLaunchKernelGGL(attn_varlen_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, t,
+                           total, a.queue);
+      });
+}
+
+hipError_t launch_attention_varlen(const AttnArgs& a, const SeqTable& t, hipStream_t s) {
   const AttnCore c = make_attn_core(a);
-  int grid = 0;
-#define RBS_ATTN_VARLEN_CASE(BSZ)                                                                              \
-  case BSZ:                                                                                                    \
-    if (a.queue == nullptr) {                                                                                  \
-      hipLaunchKernelGGL(attn_varlen_kernel<BSZ>, dim3(total), dim3(BSZ * 2), 0, s, c, a.counts, a.indices, t); \
-    } else {                                                                                                   \
-      hipError_t e = resident_grid<attn_varlen_queue_kernel<BSZ>>(BSZ * 2, total, &grid);                      \
-      if (e == hipSuccess) e = reset_queues(a.queue, s);                                                       \
-      if (e != hipSuccess) return e;                                                                           \
-      hipLaunchKernelGGL(attn_varlen_queue_kernel<BSZ>, dim3(grid), dim3(BSZ * 2), 0, s, c, a.counts,         \
-                         a.indices, t, total, a.queue);                                                        \
-    }                                                                                                          \
-    break;
   switch (a.block_size) {
-    RBS_ATTN_VARLEN_CASE(64)
-    RBS_ATTN_VARLEN_CASE(128)
-    RBS_ATTN_VARLEN_CASE(256)
+    case 64: return launch_attention_varlen_bs<64>(c, a, t, s);
+    case 128: return launch_attention_varlen_bs<128>(c, a, t, s);
+    case 256: return launch_attention_varlen_bs<256>(c, a, t, s);
     default: return hipErrorInvalidValue;
   }
-#undef RBS_ATTN_VARLEN_CASE
-  return hipGetLastError();
 }
 
 hipError_t launch_dense_indices_varlen(int n_q_heads, const SeqTable& t, int32_t* counts, int32_t* indices,

@@ -473,17 +473,10 @@ hipError_t launch_fp8_pack(const uint16_t* Q, const uint16_t* K, const uint16_t*
 
 template <int BS>
 static hipError_t launch_attention_fp8_bs(const AttnF8Args& a, int* queue, hipStream_t s) {
-  const int total = a.M * a.Hq;
-  if (queue == nullptr) {
-    hipLaunchKernelGGL(attn_fp8_kernel<BS>, dim3(total), dim3(BS * 2), 0, s, a);
-    return hipGetLastError();
-  }
-  int grid = 0;
-  hipError_t e = resident_grid<attn_fp8_queue_kernel<BS>>(BS * 2, total, &grid);
-  if (e == hipSuccess) e = reset_queues(queue, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_fp8_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, queue);
-  return hipGetLastError();
+  return launch_slots<attn_fp8_queue_kernel<BS>>(
+      BS * 2, a.M * a.Hq, queue, s,
+      [&](int grid) { hipLaunchKernelGGL(attn_fp8_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a); },
+      [&](int grid) { hipLaunchKernelGGL(attn_fp8_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, queue); });
 }
 
 hipError_t launch_attention_fp8(const uint8_t* Q8, const uint8_t* K8, const uint8_t* V8t, const float* amax,

@@ -73,17 +73,60 @@ def test_queue_with_fewer_items_than_queues():
                  "2 items")
 
 
-@pytest.mark.parametrize("heads,blocks", [(1, 1), (1, 7), (1, 8), (3, 3), (1, 17), (8, 8), (1, 65)])
-def test_queue_item_counts_around_the_queue_count(heads, blocks):
-    """1 to 65 items over the 8 queues: empty queues, queues of unequal length
-    and a last ticket in each, where a workgroup goes from queue to queue and
-    has to stop once all are empty."""
-    w = WORKLOADS["tiny-2k"].with_(name="queue-count", seq_len=64 * blocks - 5, n_q_heads=heads, n_kv_heads=1,
-                                   block_size=64, needles_per_kv_head=0, seed=50 + blocks)
-    _say(f"[queue] {heads * blocks} items")
-    shape, Q, K, V, counts, indices = _setup(w, dense=True)
-    _assert_same(_attend(shape, Q, K, V, counts, indices, None), _attend(shape, Q, K, V, counts, indices, "auto"),
-                 f"{heads * blocks} items")
+@pytest.mark.parametrize("extra", [-1, 0, 1, 7, 9])
+def test_item_counts_around_the_resident_count(extra):
+    """A call takes the queues once it has more items than the GPU holds
+    workgroups (two per compute unit at B = 128).  Just past that the queues
+    hold unequal numbers of tickets, most workgroups find their second ticket
+    past the end, and each has to stop once all eight are empty."""
+    import torch
+    items = 2 * torch.cuda.get_device_properties(0).multi_processor_count + extra
+    w = WORKLOADS["tiny-2k"].with_(name="queue-count", seq_len=128 * items - 5, n_q_heads=1, n_kv_heads=1,
+                                   block_size=128, needles_per_kv_head=0, seed=50)
+    _say(f"[queue] {items} items")
+    shape, Q, K, V, counts, indices = _setup(w)
+    ws = torch.full((64,), -5, dtype=torch.int32, device="cuda")  # stale contents
+    _assert_same(_attend(shape, Q, K, V, counts, indices, None), _attend(shape, Q, K, V, counts, indices, ws),
+                 f"{items} items")
+
+
+@pytest.mark.parametrize("B", [64, 128, 256])
+def test_queues_with_more_items_than_resident(B):
+    """Every call that takes the queues, with 1.1 times the items that the GPU
+    holds: equal to the one-workgroup-per-item launch, and replayed from a
+    graph with eager calls on the same workspace between the replays."""
+    import torch
+    import paper_2609_20971_amd as rbs
+    w = WORKLOADS["tiny-2k"].with_(name="queue-many", seq_len=4480, n_q_heads=16, n_kv_heads=2, block_size=B,
+                                   seed=60 + B)
+    _say(f"[queue] B={B} {16 * w.n_blocks} items")
+    shape, Q, K, V, counts, indices = _setup(w)
+    ws = torch.full((64,), -5, dtype=torch.int32, device="cuda")
+    ref = _attend(shape, Q, K, V, counts, indices, None)
+    _assert_same(ref, _attend(shape, Q, K, V, counts, indices, ws), "bf16")
+
+    f8 = rbs.rbs_fp8_prepare(shape, Q, K, V)
+    out8 = [rbs.rbs_sparse_prefill_fp8(shape, f8, counts, indices, workspace=x) for x in (None, ws)]
+    torch.cuda.synchronize()
+    assert torch.equal(out8[0], out8[1]), "fp8"
+
+    batch = rbs.Batch([3000, 901, 579])
+    bshape = rbs.varlen_shape(batch, 16, 2, B)
+    bc, bi = rbs.rbs_dense_indices_varlen(bshape, batch)
+    outb = [rbs.rbs_sparse_prefill_varlen(bshape, batch, Q, K, V, bc, bi, workspace=x) for x in (None, ws)]
+    torch.cuda.synchronize()
+    assert torch.equal(outb[0], outb[1]), "varlen"
+
+    O, lse = torch.empty_like(Q), torch.empty_like(ref[1])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        rbs.rbs_sparse_prefill(shape, Q, K, V, counts, indices, 0.0, O, lse=lse, workspace=ws)
+    for rep in range(3):
+        O.zero_()
+        lse.fill_(7.0)
+        g.replay()
+        _assert_same((O, lse), ref, f"replay {rep}")
+        _assert_same(_attend(shape, Q, K, V, counts, indices, ws), ref, f"eager call after replay {rep}")
 
 
 def test_caller_workspace_with_stale_contents_and_reuse():

@@ -139,12 +139,12 @@ int64_t rbs_index_capacity(int32_t n_blocks);
  *   non-NULL  a persistent grid (as many workgroups as the GPU holds at once)
  *             takes the same (query head, query block) items from per-XCD work
  *             queues held in the workspace.  Each XCD runs the same items in
- *             the same order as with NULL, so results are bit-identical; the
+ *             the same order as with NULL, and results are bit-identical; the
  *             launch avoids the idle workgroup slots that in-order dispatch of
  *             rows of very different lengths leaves (a sparse selection's
- *             rows differ by an order of magnitude).  A call with no more
- *             items than that runs them all at once, one workgroup each, and
- *             leaves the workspace alone.
+ *             rows differ by an order of magnitude).  A call with
+ *             few items for the GPU's size runs one workgroup each all the
+ *             same and leaves the workspace alone.
  * The call resets the queues itself (with a kernel on `stream`, no memset):
  * contents on entry are ignored and undefined afterwards.  The workspace is
  * written by the call like an output, so calls that share one must be

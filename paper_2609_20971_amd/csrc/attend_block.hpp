@@ -144,6 +144,7 @@ struct AttnCore {
   int64_t kv_head, kv_tok;  // the same for K and V
   int N, M, group;
   int ld;  // tokens between consecutive heads of lse (N, or the batch's total)
+  bool row_major;  // work order (work_of)
   float scale_log2;
   uint16_t* O;
   float* lse;
@@ -154,9 +155,11 @@ struct AttnCore {
 // B/32 waves of the calling workgroup.  k_lds and v_lds: B * 256 bytes of LDS
 // each, 256-byte aligned.  VARLEN: the lse head stride c.ld differs from N (a
 // sequence of a batch); otherwise it is N and c.ld is not read.
-template <int BS, bool VARLEN = false, typename ListAt>
+// last_block(): called by every wave as the last listed block begins (again if
+// the item restarts; not at all for an empty list).
+template <int BS, bool VARLEN = false, typename ListAt, typename LastBlock>
 __device__ __forceinline__ void attend_block(const AttnCore& c, int h, int i, int count, ListAt list_at,
-                                             unsigned char* k_lds, unsigned char* v_lds) {
+                                             unsigned char* k_lds, unsigned char* v_lds, LastBlock last_block) {
   constexpr int SUB = BS < 128 ? BS : 128;  // keys per softmax step
   constexpr int KT = SUB / 32;              // 32-key MFMA tiles per step
   const uint16_t* __restrict__ Q = c.Q;
@@ -305,6 +308,7 @@ __device__ __forceinline__ void attend_block(const AttnCore& c, int h, int i, in
     // still be in flight.
     if (v_spread) RBS_WAIT_VMCNT(kCopyHead); else RBS_WAIT_VMCNT(8);
     __syncthreads();
+    if (!has_next) last_block();
 
     // Softmax steps of a block kept as a loop: unrolled, B = 256's two steps
     // spilled inside the block loop (~230 scratch accesses per block).
@@ -483,21 +487,22 @@ __device__ __forceinline__ void attend_block(const AttnCore& c, int h, int i, in
 }
 
 
-// Work slot id (of total) -> (query head, query block): KV-group-major, late
-// rows first within a group, the group's query heads adjacent (and, through
-// xcd_remap, on one XCD).
-__device__ __forceinline__ void work_of(int id, int total, int M, int group, int& h, int& i) {
+// Work slot id (of total = M hq) -> (query head, query block), late (long)
+// rows first, a group's query heads adjacent (and, through xcd_remap, on one
+// XCD).  Two orders: KV-group-major (all rows of one KV group, then the next),
+// or row-major (one query block of every head, then the block before it).
+__device__ __forceinline__ void work_of(int id, int total, int M, int hq, int group, bool row_major, int& h, int& i) {
   const int work = xcd_remap(id, total);
+  if (row_major) {
+    i = M - 1 - work / hq;
+    h = work % hq;
+    return;
+  }
   const int per_group = M * group;
   const int g = work / per_group;
   const int rem = work - g * per_group;
   i = M - 1 - rem / group;
   h = g * group + rem % group;
-}
-
-// One workgroup per work slot: the slot is the workgroup id.
-__device__ __forceinline__ void work_item(int M, int group, int& h, int& i) {
-  work_of(blockIdx.x, gridDim.x, M, group, h, i);
 }
 
 // Work queues of the persistent launches.  The hardware sends workgroup j to
@@ -513,13 +518,32 @@ __device__ __forceinline__ void work_item(int M, int group, int& h, int& i) {
 // tail of the slower ones.  kQueueInts int32 counters, zeroed by reset_queues
 // before each launch.
 
-// The queue a workgroup takes its first tickets from.
-__device__ __forceinline__ int first_queue() { return (int)(blockIdx.x & (kQueues - 1)); }
+// A workgroup's place in the queues: the queue it takes tickets from, and its
+// next ticket of that queue (wave 0's lanes; valid when `taken`).
+struct QueueTicket {
+  int* queue;
+  int q;
+  int t;
+  bool taken;
+
+  __device__ __forceinline__ explicit QueueTicket(int* counters)
+      : queue(counters), q((int)(blockIdx.x & (kQueues - 1))), t(0), taken(false) {}
+
+  // Wave 0 takes a ticket (one increment, made by its lane 0; the other lanes
+  // add zero).  Called as an item's last block begins, the atomic's round trip
+  // (~2.5 us across the XCDs) runs beside that block's work; called earlier, a
+  // workgroup would hold an item that others could run.
+  __device__ __forceinline__ void take() {
+    if (taken) return;
+    taken = true;
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
+      t = atomicAdd(queue + kQueueStride * q, (threadIdx.x & 63) == 0 ? 1 : 0);
+  }
+};
 
 // The next work slot (< total) for this workgroup, the same value in every
-// thread, or -1 once every queue is empty.  Wave 0 takes a ticket (one
-// increment, made by its lane 0; the other lanes add zero) and passes it
-// through LDS; the barrier makes it visible and is also the one every wave
+// thread, or -1 once every queue is empty.  Wave 0 passes its ticket through
+// LDS; the barrier makes it visible and is also the one every wave
 // passes before the tiles of the previous item may be overwritten.  A ticket
 // past the end of its queue means the queue is empty (tickets only grow); the
 // wave then looks at all eight counters at once (lane l reads counter l % 8)
@@ -527,33 +551,34 @@ __device__ __forceinline__ int first_queue() { return (int)(blockIdx.x & (kQueue
 // costs a workgroup two round trips and not one per queue (700 dense tokens, 32
 // heads, B = 128: 44.6 -> 25.7 us; 2048 tokens, 2 heads, B = 64: 67.4 -> 49.0
 // us).  Control flow around the barriers is uniform.
-__device__ __forceinline__ int next_slot(int* queue, int total, int* lds_slot, int& q) {
+__device__ __forceinline__ int next_slot(QueueTicket& k, int total, int* lds_slot) {
   for (;;) {
+    k.take();
+    k.taken = false;
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
-      const int lane = threadIdx.x & 63;
-      const int t = __builtin_amdgcn_readfirstlane(atomicAdd(queue + q, lane == 0 ? 1 : 0));
-      int next = kQueues * t + q;
+      int next = kQueues * __builtin_amdgcn_readfirstlane(k.t) + k.q;
       if (next >= total) {
-        const int l = lane & (kQueues - 1);
-        const int c = __hip_atomic_load(queue + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int l = threadIdx.x & (kQueues - 1);
+        const int c = __hip_atomic_load(k.queue + kQueueStride * l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t open = (uint32_t)__ballot(kQueues * c + l < total) & ((1u << kQueues) - 1);
         // -1: every queue is empty; -2 - p: queue p is the next one to try.
         const uint32_t ring = open | (open << kQueues);  // queues q + 1 .. q + 8, cyclically
-        next = open == 0 ? -1 : -2 - ((q + __builtin_ctz(ring >> (q + 1)) + 1) & (kQueues - 1));
+        next = open == 0 ? -1 : -2 - ((k.q + __builtin_ctz(ring >> (k.q + 1)) + 1) & (kQueues - 1));
       }
       *lds_slot = next;
     }
     __syncthreads();
     const int slot = __builtin_amdgcn_readfirstlane(*lds_slot);
     if (slot >= -1) return slot;
-    q = -2 - slot;
+    k.q = -2 - slot;
     __syncthreads();  // every wave has read lds_slot before wave 0 writes the next ticket
   }
 }
 
-// Zero the kQueueInts counters of a persistent launch (a kernel, not a memset,
-// so that the call can be captured in a graph and replayed).
-hipError_t reset_queues(int* queue, hipStream_t s);
+// Set the counters of a persistent launch of `grid` workgroups (a kernel, not a
+// memset, so that the call can be captured in a graph and replayed).  Workgroup
+// j runs slot j first, without a ticket: the counters start at grid / kQueues.
+hipError_t reset_queues(int* queue, int grid, hipStream_t s);
 
 // Workgroups of Kernel (threads each) that the device holds at once, rounded
 // down to a multiple of the queue count.  Cached per device (each kernel has
@@ -581,12 +606,15 @@ hipError_t resident_grid(int threads, int* grid) {
 }
 
 // One launch of total work slots by workgroups of `threads`: persistent
-// through the queues when there are more slots than the device holds at once
-// and the caller gave a queue, otherwise one workgroup per slot: with every
-// slot resident from the start there is nothing to hand out, and the counter
-// reset's launch and the tickets are saved (700 dense tokens, 32 heads, B =
-// 128: 25.7 -> 19.9 us; 2048 tokens, 2 heads, B = 64 layer: 64.9 -> 58.6 us).
-// With more slots than that the queues win: in-order dispatch holds slots back.
+// through the queues when the caller gave them and there are more than three
+// times as many slots as the device holds at once, otherwise one workgroup per
+// slot.  Few slots leave little to hand out, and the counter reset's launch and
+// the tickets are saved; with many, in-order dispatch holds slots back where the
+// rows' lengths differ.  Queues against per slot, 32 heads: 700 dense tokens (0.4
+// times the resident slots) 25.7 / 19.9 us, 3001 (1.5 times) 99 / 89, 6000 (3
+// times) 299 / 288 dense and 251 / 251 on sparse lists, 8100 (4 times) 518 / 507
+// dense and 397 / 438 sparse; B = 64 6000 343 / 325 and 300 / 283, 8100 590 / 566
+// and 442 / 476.
 // per_item(grid) and queued(grid) launch the two forms.
 template <auto QueueKernel, typename PerItem, typename Queued>
 hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, PerItem per_item, Queued queued) {
@@ -597,14 +625,30 @@ hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, PerIt
   int resident = 0;
   hipError_t e = resident_grid<QueueKernel>(threads, &resident);
   if (e != hipSuccess) return e;
-  if (total <= resident) {
+  if (total <= 3 * resident) {
     per_item(total);
     return hipGetLastError();
   }
-  e = reset_queues(queue, s);
+  e = reset_queues(queue, resident, s);
   if (e != hipSuccess) return e;
   queued(resident);
   return hipGetLastError();
+}
+
+// Whether a launch over n_kv_heads heads of n_tokens K and V rows (row_bytes for
+// the two together) takes its rows in row-major order.  That order starts the
+// longest rows of every head first, where the group-major order starts the
+// last group's longest rows last and ends on them alone, and it gives each XCD
+// one KV head (with up to 8) instead of all XCDs the same one; but it keeps all
+// KV heads in use at once.  The line is where they still fit the 256 MiB
+// Infinity Cache (half of it at B = 64, whose tiles are used for half as many
+// queries).  Attention, group-major against row-major: 3001 dense tokens, 32 / 4
+// heads 128 / 102 us, 8192 565 / 518, 16384 1966 / 1928, 16384 with 8 / 8 heads
+// 640 / 555, 64K with 64 / 8 heads 8.47 / 8.39 ms; past the line 128K with 64 / 8
+// heads 18.6 / 18.8 ms, 256K with 32 / 4 heads 23.3 / 23.6, 128K at B = 64 15.3 /
+// 15.45 ms.
+inline bool row_major_work(int n_tokens, int n_kv_heads, int row_bytes, int block_size) {
+  return (int64_t)n_tokens * n_kv_heads * row_bytes <= (block_size >= 128 ? 256 : 128) * (int64_t(1) << 20);
 }
 
 inline AttnCore make_attn_core(const AttnArgs& a) {
@@ -620,6 +664,7 @@ inline AttnCore make_attn_core(const AttnArgs& a) {
   c.M = a.n_blocks;
   c.group = a.n_q_heads / a.n_kv_heads;
   c.ld = a.n_tokens;
+  c.row_major = row_major_work(a.n_tokens, a.n_kv_heads, 512, a.block_size);
   c.scale_log2 = a.scale * kLog2e;
   c.O = a.O;
   c.lse = a.lse;

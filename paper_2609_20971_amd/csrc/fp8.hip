@@ -216,6 +216,7 @@ struct AttnF8Args {
   const uint8_t* V8t;
   const float* amax;  // [H_q + 2 H_kv]: Q heads, K heads, V heads
   int N, M, Hq, Hkv;
+  bool row_major;     // work order (work_of)
   float scale_log2;   // softmax scale * log2(e)
   const int32_t* counts;
   const int32_t* indices;
@@ -236,9 +237,10 @@ __device__ __forceinline__ i32x8 read_vt32(const unsigned char* v_lds, int kbase
 
 // Query block i of query head h; k_lds, v_lds: BS * 128 bytes each.  The
 // block's keys are taken in softmax steps of up to 128 (two for B = 256).
-template <int BS>
+// last_block(): called by every wave as the last listed block begins.
+template <int BS, typename LastBlock>
 __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int i, unsigned char* k_lds,
-                                                 unsigned char* v_lds) {
+                                                 unsigned char* v_lds, LastBlock last_block) {
   constexpr int SUB = BS < 128 ? BS : 128;  // keys per softmax step
   constexpr int KT = SUB / 32;              // 32-key S^T tiles per step
   constexpr int NST = SUB / 64;             // 64-key PV steps per softmax step
@@ -299,6 +301,7 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
 
     RBS_WAIT_VMCNT(4);  // this block's K has landed (its V may still be in flight)
     __syncthreads();
+    if (!has_next) last_block();
 
     // (Steps not unrolled: two unrolled 128-key steps spill heavily.)
 #pragma unroll 1
@@ -396,14 +399,14 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
   }
 }
 
-// One workgroup per (query head, query block), ordered by work_item.
+// One workgroup per (query head, query block), ordered by work_of.
 template <int BS>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_kernel(AttnF8Args c) {
   __shared__ __align__(1024) unsigned char k_lds[BS * 128];
   __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
   int h, i;
-  work_item(c.M, c.Hq / c.Hkv, h, i);
-  attend_block_fp8<BS>(c, h, i, k_lds, v_lds);
+  work_of(blockIdx.x, gridDim.x, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
+  attend_block_fp8<BS>(c, h, i, k_lds, v_lds, [] {});
 }
 
 // Persistent form (the queues of next_slot): the same work slots, on the same
@@ -415,13 +418,11 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
   __shared__ int lds_slot;
   const int total = c.M * c.Hq;
-  int q = first_queue();
-  for (;;) {
-    const int slot = next_slot(queue, total, &lds_slot, q);
-    if (slot < 0) break;
+  QueueTicket ticket(queue);
+  for (int slot = blockIdx.x; slot >= 0; slot = next_slot(ticket, total, &lds_slot)) {
     int h, i;
-    work_of(slot, total, c.M, c.Hq / c.Hkv, h, i);
-    attend_block_fp8<BS>(c, h, i, k_lds, v_lds);
+    work_of(slot, total, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
+    attend_block_fp8<BS>(c, h, i, k_lds, v_lds, [&]() __attribute__((always_inline)) { ticket.take(); });
     __syncthreads();  // tiles and lds_slot free for the next item
   }
 }
@@ -492,6 +493,7 @@ hipError_t launch_attention_fp8(const uint8_t* Q8, const uint8_t* K8, const uint
   a.M = n_blocks;
   a.Hq = n_q_heads;
   a.Hkv = n_kv_heads;
+  a.row_major = row_major_work(n_tokens, n_kv_heads, 256, block_size);
   a.scale_log2 = scale * kLog2e;
   a.counts = counts;
   a.indices = indices;

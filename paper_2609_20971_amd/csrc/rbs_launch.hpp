@@ -90,7 +90,8 @@ inline size_t summary_bytes(int n_kv_heads, int n_blocks) {
 constexpr int kMaxSeqs = 64;
 constexpr int kMaxDevices = 64;  // devices whose resident-grid size the launchers cache
 constexpr int kQueues = 8;       // work queues of a persistent attention launch, one per XCD
-constexpr int kQueueInts = 64;   // its workspace: 256 bytes, the eight counters and room to spare
+constexpr int kQueueInts = 64;   // its workspace: 256 bytes, the eight counters spread over it
+constexpr int kQueueStride = kQueueInts / kQueues;
 struct SeqTable {
   int n;
   int tok[kMaxSeqs + 1];
@@ -108,6 +109,51 @@ __host__ __device__ inline int seq_of(const int* off, int n, int x) {
     else hi = mid - 1;
   }
   return lo;
+}
+
+// The rows (query blocks) of all sequences of a batch by descending row number
+// i within their sequence, so that a launch's longest rows come first whatever
+// sequence they belong to.  Sequences sorted by descending block count:
+// seq[0], seq[1], ...; level k (1 <= k <= n) holds the row numbers that exactly
+// the first k of them have, the k rows of one number next to each other:
+// row r of level k (start[k] <= r < start[k + 1]) is number
+// blocks[k - 1] - 1 - (r - start[k]) / k of sequence seq[(r - start[k]) % k].
+struct RowOrder {
+  int n;
+  int seq[kMaxSeqs];
+  int blocks[kMaxSeqs];     // block count of seq[k]
+  int start[kMaxSeqs + 2];  // index by level; start[0] = start[1] = 0, start[n + 1] = all rows
+};
+
+inline RowOrder rows_by_length(const SeqTable& t) {
+  RowOrder o{};
+  o.n = t.n;
+  for (int q = 0; q < t.n; ++q) {  // insertion sort, stable
+    const int m = t.blk[q + 1] - t.blk[q];
+    int p = q;
+    for (; p > 0 && o.blocks[p - 1] < m; --p) {
+      o.blocks[p] = o.blocks[p - 1];
+      o.seq[p] = o.seq[p - 1];
+    }
+    o.blocks[p] = m;
+    o.seq[p] = q;
+  }
+  for (int k = 1; k <= t.n; ++k)
+    o.start[k + 1] = o.start[k] + k * (o.blocks[k - 1] - (k < t.n ? o.blocks[k] : 0));
+  return o;
+}
+
+// Row r of the order: its sequence and row number.
+__host__ __device__ inline void row_at(const RowOrder& o, int r, int* seq, int* i) {
+  int lo = 1, hi = o.n;  // the largest level with start <= r; empty levels share a start with the next one
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (o.start[mid] <= r) lo = mid;
+    else hi = mid - 1;
+  }
+  const int off = r - o.start[lo];
+  *seq = o.seq[off % lo];
+  *i = o.blocks[lo - 1] - 1 - off / lo;
 }
 
 inline SeqTable single_sequence(int n_tokens, int n_blocks) {

@@ -1060,7 +1060,7 @@ def layer_sweep(args):
 KERNEL_SOURCES = {
     "stats_kernel": ["stats.hip", "rbs_device.hpp", "../build.py"],
     "quantile_kernel": ["stats.hip", "rbs_device.hpp", "../build.py"],
-    "select_kernel": ["select.hip", "select_block.hpp", "rbs_device.hpp", "../build.py"],
+    "select_kernel": ["select.hip", "rbs_device.hpp", "../build.py"],
     "attn_queue_kernel": ["attn.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
     "attn_fp8_queue_kernel": ["fp8.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
 }

@@ -475,6 +475,8 @@ int rbs_select_variant(const rbs_shape* shape, const void* Q, const rbs_stats* s
     a.tau_base = a.tau_rescue = 1.f;  // unused
   } else {
     a.cent16 = static_cast<const _Float16*>(stats->summary);
+    a.cnorm = reinterpret_cast<const float*>(static_cast<const unsigned char*>(stats->summary) +
+                                             rbs::summary_cnorm_offset(shape->n_kv_heads, M));
     a.tau_base = a.tau_rescue = param;
   }
   a.uplift = nullptr;

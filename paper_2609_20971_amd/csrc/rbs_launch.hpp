@@ -40,11 +40,11 @@ struct SelectArgs {
   const uint16_t* Q;
   int64_t q_head, q_tok;  // Q strides
   int n_tokens, n_q_heads, n_kv_heads, block_size, n_blocks;
-  int mode = 0;                       // SelectMode (select_block.hpp)
+  int mode = 0;                       // SelectMode (select.hip)
   const _Float16* cent16;             // box: scaled box centres
   const _Float16* half16 = nullptr;   // box: scaled box half-widths
   const float* uplift;
-  const float* cnorm = nullptr;       // dual: select-ready centroid norms
+  const float* cnorm = nullptr;       // select-ready centroid norms (not the box's)
   const float* radii = nullptr;       // full-L2
   float budget = 0.f;                 // box: budget fraction
   float tau_base, tau_rescue;

@@ -115,6 +115,46 @@ def test_multiblock_rows(variant):
     _full_check(w, attn_rows=attn)
 
 
+@pytest.mark.parametrize("n,heads,block_size", [
+    (128 * 320 - 3, (3, 1), 128),   # rows shared by two waves (up to 320 blocks), 3 heads: rows of different blocks
+    (128 * 321, (3, 1), 128),       # one wave per row, four rows a workgroup, the last workgroup partial
+    (128 * 321 + 1, (5, 5), 128),   # no GQA: every row of a workgroup another query block; a last block of one token
+    (64 * 65 + 33, (7, 1), 64),     # 66 blocks, a last block of 33 tokens (a full group of 32 and one token)
+    (256 * 33 + 64, (2, 1), 256),   # rows shared by four waves, two of them without a token in the last block
+    (64 * 3900, (1, 1), 64),        # score rows too long for four rows a workgroup
+])
+def test_selection_row_splits(n, heads, block_size):
+    """Selection at the edges of its split of rows over waves and workgroups."""
+    import torch
+    import paper_2609_20971_amd as rbs
+    w = WORKLOADS["tiny-2k"].with_(name="split", seq_len=n, n_q_heads=heads[0], n_kv_heads=heads[1],
+                                   block_size=block_size, needles_per_kv_head=6, seed=71)
+    _say(f"[parity] selection split N={n} heads={heads} B={block_size}")
+    inp = make_inputs(w)
+    shape = rbs.make_shape(n, *heads, block_size)
+    Qd, Kd = H.to_device(inp["q"]), H.to_device(inp["k"])
+    st = rbs.rbs_block_stats(shape, Kd)
+    M = w.n_blocks
+    rows = H.sample_rows(heads[0], M, 24, seed=3, include=[(0, M - 1), (heads[0] - 1, M - 1), (0, M - 2), (0, 0),
+                                                           (heads[0] - 1, min(M - 1, 32)), (0, min(M - 1, 64))])
+    C, R = oracle.block_stats(f64_from_bf16_bits(inp["k"]), block_size)
+    beta, _ = oracle.rescue_coefficients(R)
+    Qf = f64_from_bf16_bits(inp["q"])
+    # The second pair of thresholds lets the rescue branch score most blocks.
+    for tau in ((0.9, 0.95), (0.9, 0.2)):
+        counts, indices = rbs.rbs_select(shape, Qd, st, *tau, w.n_sink, w.n_local, w.n_recent)
+        torch.cuda.synchronize()
+        ref = oracle.select(Qf, C, R, beta, block_size, *tau, w.n_sink, w.n_local, w.n_recent, rows=rows)
+        lists = H.gpu_rows(counts, indices, rows)
+        H.check_lists(lists, M, w.n_sink, w.n_local, w.n_recent)
+        H.compare_masks(lists, ref)
+        every = [(h, i) for h in range(heads[0]) for i in range(M)]
+        H.check_lists(H.gpu_rows(counts, indices, every), M, w.n_sink, w.n_local, w.n_recent)
+    del ref
+    for variant, param in (("centroid", 0.9), ("full_l2", 0.9), ("box", 0.1)):
+        _variant_check(w, variant, param, rows=rows[:12], inputs=inp)
+
+
 @pytest.mark.parametrize("tau,forced", [
     ((0.0, 0.0), (1, 2, 0)),     # alpha = 0: every causal block
     ((1.0, 1.0), (0, 1, 0)),     # alpha = 1: argmax blocks only

@@ -529,15 +529,15 @@ struct QueueTicket {
   __device__ __forceinline__ explicit QueueTicket(int* counters)
       : queue(counters), q((int)(blockIdx.x & (kQueues - 1))), t(0), taken(false) {}
 
-  // Wave 0 takes a ticket (one increment, made by its lane 0; the other lanes
-  // add zero).  Called as an item's last block begins, the atomic's round trip
+  // Lane 0 of wave 0 takes a ticket.  (The other lanes adding zero instead of
+  // standing aside made the compiler sum the wave's 64 addends in a scalar loop
+  // first, ~1 us.)  Called as an item's last block begins, the atomic's round trip
   // (~2.5 us across the XCDs) runs beside that block's work; called earlier, a
   // workgroup would hold an item that others could run.
   __device__ __forceinline__ void take() {
     if (taken) return;
     taken = true;
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0)
-      t = atomicAdd(queue + kQueueStride * q, (threadIdx.x & 63) == 0 ? 1 : 0);
+    if (threadIdx.x == 0) t = atomicAdd(queue + kQueueStride * q, 1);
   }
 };
 

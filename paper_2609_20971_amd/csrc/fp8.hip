@@ -16,7 +16,13 @@
 //                 chunks XOR-swizzled), online softmax in fp32 in steps of up
 //                 to 128 keys, P rounded to E4M3.
 //                 The softmax denominator is accumulated by the matrix core
-//                 too (ones times P^T), from exactly the rounded P.
+//                 too (ones times P^T), from exactly the rounded P.  Bound by
+//                 its vector work (64 exponentials, 64 FMAs, 32 row-maximum ops
+//                 and 32 conversions per 128 keys and wave against 1090 matrix
+//                 cycles).  40961 tokens, 32 / 4 heads, partly shared lists:
+//                 B = 128 1911 us; with the denominator on 16x16x128 ops 1850;
+//                 with the lists read through scalar loads (a vector load's
+//                 wait held every block until its tile copies had landed) 1773.
 //
 // Dequantisation: amax / 448 per head, folded into the logit scale (q, k) and
 // the output normalisation (v).
@@ -218,9 +224,7 @@ struct AttnF8Args {
   int N, M, Hq, Hkv;
   bool row_major;     // work order (work_of)
   float scale_log2;   // softmax scale * log2(e)
-  const int32_t* counts;
-  const int32_t* indices;
-  int64_t capacity;
+  int64_t capacity;   // list slots per query head
   uint16_t* O;
   int64_t o_head, o_tok;  // element strides of O (those of the bf16 Q)
   float* lse;
@@ -235,12 +239,14 @@ __device__ __forceinline__ i32x8 read_vt32(const unsigned char* v_lds, int kbase
   return read_row32(v_lds, kbase + d, 2 * st + half);                   // 128-key sub-tile kbase / 128
 }
 
-// Query block i of query head h; k_lds, v_lds: BS * 128 bytes each.  The
+// Query block i of query head h; counts and indices come as restricted pointers
+// so that the list is read by scalar loads; k_lds, v_lds: BS * 128 bytes each.  The
 // block's keys are taken in softmax steps of up to 128 (two for B = 256).
 // last_block(): called by every wave as the last listed block begins.
 template <int BS, typename LastBlock>
-__device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int i, unsigned char* k_lds,
-                                                 unsigned char* v_lds, LastBlock last_block) {
+__device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int32_t* __restrict__ counts,
+                                                 const int32_t* __restrict__ indices, int h, int i,
+                                                 unsigned char* k_lds, unsigned char* v_lds, LastBlock last_block) {
   constexpr int SUB = BS < 128 ? BS : 128;  // keys per softmax step
   constexpr int KT = SUB / 32;              // 32-key S^T tiles per step
   constexpr int NST = SUB / 64;             // 64-key PV steps per softmax step
@@ -252,8 +258,8 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
   const int q_local = 32 * wave + l32;
   const int qpos = i * BS + q_local;
   const bool q_ok = qpos < N;
-  const int count = min(max(c.counts[(size_t)h * c.M + i], 0), i + 1);
-  const int32_t* list = c.indices + (int64_t)h * c.capacity + (int64_t)i * (i + 1) / 2;
+  const int count = min(max(counts[(size_t)h * c.M + i], 0), i + 1);
+  const int32_t* list = indices + (int64_t)h * c.capacity + (int64_t)i * (i + 1) / 2;
   const float sl = c.scale_log2 * (fp8_deq_scale(c.amax[h]) * fp8_deq_scale(c.amax[c.Hq + g]));
   const float v_deq = fp8_deq_scale(c.amax[c.Hq + c.Hkv + g]);
 
@@ -273,15 +279,22 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
 
   const uint8_t* kg = c.K8 + (size_t)g * N * kHeadDim;
   const uint8_t* vg = c.V8t + (size_t)g * c.M * kHeadDim * BS;
-  i32x8 ones;
+  // Denominator on the matrix core.  Read as the B operand of the 16x16x128 op,
+  // lane l's P bytes (query l % 32, 32 keys of the step) sit in column l % 16 at
+  // k-group l / 16: groups 0 and 2 hold the keys of query l % 16, groups 1 and 3
+  // those of query l % 16 + 16.  A row m of A that is 1.0 in the k-groups of
+  // parity m % 2 sums them; lane l finds its own query's sum in element
+  // (l / 16) % 2 (rows 4 (l / 16) .. of column l % 16).  Half the matrix time and
+  // a quarter of the accumulators of a 32x32x64 op on ones.
+  i32x8 lsel;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) ones[e] = 0x38383838;  // E4M3 1.0 in every byte
+  for (int e = 0; e < 8; ++e) lsel[e] = ((lane >> 4) & 1) == (lane & 1) ? 0x38383838 : 0;  // E4M3 1.0 in every byte
 
   float ms_run = -INFINITY;
   f32x16 o[4];
 #pragma unroll
   for (int dt = 0; dt < 4; ++dt) o[dt] = f32x16{};
-  f32x16 lsum = {};  // every element: the running softmax denominator of this lane's query
+  f32x4 lacc = {};  // the running softmax denominator (see lsel)
 
   // Each tile is BS rows of 128 bytes (V^T: see vt_offset); a wave copies 32
   // rows with 4 copies per lane, so 4 copies per lane per tile.
@@ -321,13 +334,17 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
           issue_tile8(kg + (size_t)kb_next * BS * kHeadDim, min(BS, N - kb_next * BS), k_base, wave, lane);
       }
       if (diag || nk < BS) {
+        // Keys past the block's end, and on the diagonal past the query.  The
+        // limit is opaque: its 64 compare masks, kept for the whole loop, took
+        // 116 scalar and 9 vector registers to scratch.
+        const int limit = diag ? min(q_local, nk - 1) : nk - 1;
 #pragma unroll
-        for (int mt = 0; mt < KT; ++mt)
+        for (int mt = 0; mt < KT; ++mt) {
+          int lim = limit - kbase - 32 * mt - 4 * half;
+          asm volatile("" : "+v"(lim));
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kbase + 32 * mt + mfma_row(r, lane);
-            if (key >= nk || (diag && key > q_local)) s[mt][r] = -INFINITY;
-          }
+          for (int r = 0; r < 16; ++r) s[mt][r] = 8 * (r >> 2) + (r & 3) > lim ? -INFINITY : s[mt][r];
+        }
       }
       float mx = -INFINITY;
 #pragma unroll
@@ -341,7 +358,7 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
         const float alpha = ms_new == ms_run ? 1.f : fast_exp2(ms_run - ms_new);
         ms_run = ms_new;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) lsum[r] *= alpha;
+        for (int e = 0; e < 4; ++e) lacc[e] *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -370,7 +387,7 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
           o[dt] = mfma_f8(read_vt32<BS>(v_lds, kbase, 32 * dt + l32, st, half), pk[st], o[dt]);
-        lsum = mfma_f8(ones, pk[st], lsum);
+        lacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(lsel, pk[st], lacc, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
       }
     }
     __syncthreads();  // every wave is done with this V tile
@@ -378,7 +395,7 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
     kb = kb_next;
   }
 
-  const float l_tot = lsum[0];
+  const float l_tot = ((lane >> 4) & 1) ? lacc[1] : lacc[0];
   const float inv = l_tot > 0.f ? v_deq / l_tot : 0.f;
   if (q_ok) {
     uint16_t* orow = c.O + h * c.o_head + (int64_t)qpos * c.o_tok;
@@ -401,19 +418,20 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, int h, int
 
 // One workgroup per (query head, query block), ordered by work_of.
 template <int BS>
-__global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_kernel(AttnF8Args c) {
+__global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_kernel(
+    AttnF8Args c, const int32_t* __restrict__ counts, const int32_t* __restrict__ indices) {
   __shared__ __align__(1024) unsigned char k_lds[BS * 128];
   __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
   int h, i;
   work_of(blockIdx.x, gridDim.x, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
-  attend_block_fp8<BS>(c, h, i, k_lds, v_lds, [] {});
+  attend_block_fp8<BS>(c, counts, indices, h, i, k_lds, v_lds, [] {});
 }
 
 // Persistent form (the queues of next_slot): the same work slots, on the same
 // XCDs in the same order apart from the tail, bit-identical results.
 template <int BS>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_queue_kernel(
-    AttnF8Args c, int* __restrict__ queue) {
+    AttnF8Args c, const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, int* __restrict__ queue) {
   __shared__ __align__(1024) unsigned char k_lds[BS * 128];
   __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
   __shared__ int lds_slot;
@@ -422,7 +440,7 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   for (int slot = blockIdx.x; slot >= 0; slot = next_slot(ticket, total, &lds_slot)) {
     int h, i;
     work_of(slot, total, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
-    attend_block_fp8<BS>(c, h, i, k_lds, v_lds, [&]() __attribute__((always_inline)) { ticket.take(); });
+    attend_block_fp8<BS>(c, counts, indices, h, i, k_lds, v_lds, [&]() __attribute__((always_inline)) { ticket.take(); });
     __syncthreads();  // tiles and lds_slot free for the next item
   }
 }
@@ -473,11 +491,12 @@ hipError_t launch_fp8_pack(const uint16_t* Q, const uint16_t* K, const uint16_t*
 }
 
 template <int BS>
-static hipError_t launch_attention_fp8_bs(const AttnF8Args& a, int* queue, hipStream_t s) {
+static hipError_t launch_attention_fp8_bs(const AttnF8Args& a, const int32_t* counts, const int32_t* indices,
+                                          int* queue, hipStream_t s) {
   return launch_slots<attn_fp8_queue_kernel<BS>>(
       BS * 2, a.M * a.Hq, queue, s,
-      [&](int grid) { hipLaunchKernelGGL(attn_fp8_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a); },
-      [&](int grid) { hipLaunchKernelGGL(attn_fp8_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, queue); });
+      [&](int grid) { hipLaunchKernelGGL(attn_fp8_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, counts, indices); },
+      [&](int grid) { hipLaunchKernelGGL(attn_fp8_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, counts, indices, queue); });
 }
 
 hipError_t launch_attention_fp8(const uint8_t* Q8, const uint8_t* K8, const uint8_t* V8t, const float* amax,
@@ -495,17 +514,15 @@ hipError_t launch_attention_fp8(const uint8_t* Q8, const uint8_t* K8, const uint
   a.Hkv = n_kv_heads;
   a.row_major = row_major_work(n_tokens, n_kv_heads, 256, block_size);
   a.scale_log2 = scale * kLog2e;
-  a.counts = counts;
-  a.indices = indices;
   a.capacity = capacity;
   a.O = O;
   a.o_head = o_head;
   a.o_tok = o_tok;
   a.lse = lse;
   switch (block_size) {
-    case 64: return launch_attention_fp8_bs<64>(a, queue, s);
-    case 128: return launch_attention_fp8_bs<128>(a, queue, s);
-    case 256: return launch_attention_fp8_bs<256>(a, queue, s);
+    case 64: return launch_attention_fp8_bs<64>(a, counts, indices, queue, s);
+    case 128: return launch_attention_fp8_bs<128>(a, counts, indices, queue, s);
+    case 256: return launch_attention_fp8_bs<256>(a, counts, indices, queue, s);
     default: return hipErrorInvalidValue;
   }
 }

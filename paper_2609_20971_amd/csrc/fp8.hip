@@ -3,7 +3,7 @@
 // gfx950 FP8 matrix core (v_mfma_scale_f32_32x32x64_f8f6f4, twice the bf16
 // rate).  Three kernels:
 //
-//   fp8_amax      per head, the largest |x| of Q, K and V (one pass over each).
+//   fp8_amax      per head, the largest |x| of Q, K and V (one pass).
 //   fp8_pack      x * (448 / amax) rounded to E4M3 (round to nearest even,
 //                 saturating): Q and K row-major, V as per-block transposed
 //                 tiles V^T [d][keys] whose key order matches the register
@@ -86,28 +86,59 @@ __global__ void fp8_zero_kernel(uint32_t* __restrict__ x, int n) {
   if (i < n) x[i] = 0u;
 }
 
-// 16-byte chunk c (token c / 16, dimensions 8 (c % 16) ..) of head `head` of a
-// bf16 tensor with element strides (head_stride, tok_stride).
-__device__ __forceinline__ uint4 load_chunk(const uint16_t* X, int64_t head_stride, int64_t tok_stride, int head,
-                                            int64_t c) {
-  return *reinterpret_cast<const uint4*>(X + head * head_stride + (c >> 4) * tok_stride + 8 * (c & 15));
+// The bf16 inputs of one packing call.  Heads are numbered as in amax: Q heads,
+// K heads, V heads.
+struct Fp8Inputs {
+  const uint16_t* Q;
+  const uint16_t* K;
+  const uint16_t* V;
+  Strides st;
+  int N, Hq, Hkv;
+};
+
+// First element of a head and its token stride.
+__device__ __forceinline__ const uint16_t* head_rows(const Fp8Inputs& in, int head, int64_t* tok_stride) {
+  if (head < in.Hq) {
+    *tok_stride = in.st.q_tok;
+    return in.Q + head * in.st.q_head;
+  }
+  *tok_stride = in.st.kv_tok;
+  const int g = head - in.Hq;
+  return g < in.Hkv ? in.K + g * in.st.kv_head : in.V + (g - in.Hkv) * in.st.kv_head;
 }
 
-// Largest |x| of every head of a bf16 tensor of N tokens; blockIdx.y = head,
-// blockIdx.x strides over the head's 16-byte chunks.  Non-negative floats order
-// like their bit patterns, so the maximum is an integer atomic max.
-__global__ __launch_bounds__(256) void fp8_amax_kernel(const uint16_t* __restrict__ X, int64_t head_stride,
-                                                       int64_t tok_stride, int64_t chunks_per_head,
-                                                       uint32_t* __restrict__ amax_bits) {
+// 16-byte chunk c (token c / 16, dimensions 8 (c % 16) ..) of a head.
+__device__ __forceinline__ uint4 load_chunk(const uint16_t* rows, int64_t tok_stride, int c) {
+  return *reinterpret_cast<const uint4*>(rows + (c >> 4) * tok_stride + 8 * (c & 15));
+}
+
+constexpr int kAmaxStep = 8 * 256;  // chunks of a workgroup's step: eight loads in flight per thread
+constexpr int kAmaxOneSteps = 8;    // a head of up to this many steps (1024 tokens) is one workgroup's
+
+// Largest |x| of every head; blockIdx.y = head, blockIdx.x strides over its
+// chunks.  Non-negative floats order like their bit patterns, so the maximum over
+// workgroups is an integer atomic max (over zeros), or the one workgroup's store.
+// HBM-bound: one launch for Q, K and V and eight loads in flight (a launch per
+// tensor, one load each: K and V of 40961 tokens, 4 heads 23.7 us apiece, 1.8
+// TB/s).
+__global__ __launch_bounds__(256) void fp8_amax_kernel(const Fp8Inputs in, uint32_t* __restrict__ amax_bits) {
   const int head = blockIdx.y;
+  int64_t tok;
+  const uint16_t* rows = head_rows(in, head, &tok);
+  const int chunks = in.N * (kHeadDim / 8);
   float m = 0.f;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < chunks_per_head;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    const uint4 v = load_chunk(X, head_stride, tok_stride, head, c);
-    float f[8];
-    unpack8(v, f);
+  for (int base = blockIdx.x * kAmaxStep; base < chunks; base += gridDim.x * kAmaxStep) {
+    uint4 v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(f[e]));
+    for (int k = 0; k < 8; ++k)  // (past the end: the last chunk again)
+      v[k] = load_chunk(rows, tok, min(base + 256 * k + (int)threadIdx.x, chunks - 1));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      float f[8];
+      unpack8(v[k], f);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(f[e]));
+    }
   }
 #pragma unroll
   for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, wave_xor_f(m, s));
@@ -116,72 +147,116 @@ __global__ __launch_bounds__(256) void fp8_amax_kernel(const uint16_t* __restric
   if (lane == 0) red[wave] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
-    const float t = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    atomicMax(amax_bits + head, __float_as_uint(t));
+    const uint32_t t = __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+    if (gridDim.x == 1) amax_bits[head] = t;
+    else atomicMax(amax_bits + head, t);
   }
 }
 
 // ------------------------------------------------------------------ pack
 
-// Dense row-major E4M3 copy [heads][N][d] of a strided bf16 tensor: 8
-// elements per thread.
-__global__ __launch_bounds__(256) void fp8_pack_rows_kernel(const uint16_t* __restrict__ X, int64_t head_stride,
-                                                            int64_t tok_stride, int64_t chunks_per_head,
-                                                            const float* __restrict__ amax,
-                                                            uint8_t* __restrict__ X8) {
-  const int head = blockIdx.y;
-  const float inv = fp8_inv_scale(amax[head]);
-  uint2* dst = reinterpret_cast<uint2*>(X8) + (size_t)head * chunks_per_head;
-  for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < chunks_per_head;
-       c += (int64_t)gridDim.x * blockDim.x) {
-    float f[8];
-    unpack8(load_chunk(X, head_stride, tok_stride, head, c), f);
-    uint2 o;
-    o.x = (uint32_t)pack4_fp8(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv);
-    o.y = (uint32_t)pack4_fp8(f[4] * inv, f[5] * inv, f[6] * inv, f[7] * inv);
-    dst[c] = o;
-  }
+// Eight bf16 of a chunk, scaled and rounded: eight E4M3 bytes.
+__device__ __forceinline__ uint2 pack_chunk(const uint4& v, float inv) {
+  float f[8];
+  unpack8(v, f);
+  uint2 o;
+  o.x = (uint32_t)pack4_fp8(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv);
+  o.y = (uint32_t)pack4_fp8(f[4] * inv, f[5] * inv, f[6] * inv, f[7] * inv);
+  return o;
 }
 
-// V^T tiles: workgroup (key block kb, KV head g) reads the block's B x d bf16
-// values, rounds them to E4M3 into LDS [key][d], and writes the d x B tile with
-// the keys in vt_key order, laid out by vt_offset (keys past N are zero).
+constexpr int kPackChunks = 4 * 256;  // chunks of a workgroup packing rows: four loads in flight per thread
+// Words between the keys of a V tile staged in LDS: one of padding, so that the
+// transposing reads (rows 4, 32 or 64 keys apart) hit few banks twice.
+constexpr int kVtRowWords = kHeadDim / 4 + 1;
+
+// Byte k of each of four dwords (rows), as one dword: row r of the result holds
+// byte r of rows a, b, c, d.
+__device__ __forceinline__ void transpose4x4(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t* out) {
+  const uint32_t ab_lo = __builtin_amdgcn_perm(b, a, 0x05010400u), cd_lo = __builtin_amdgcn_perm(d, c, 0x05010400u);
+  const uint32_t ab_hi = __builtin_amdgcn_perm(b, a, 0x07030602u), cd_hi = __builtin_amdgcn_perm(d, c, 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
+}
+
+// All of a packing call in one launch: workgroups 0 .. M Hkv - 1 write V^T tiles,
+// the next ones the rows of K and then of Q, last heads first -- the reverse of
+// the order in which fp8_amax_kernel reads them, so that what it read last is
+// still in the Infinity Cache.
+//   rows  kPackChunks chunks of one head: dense row-major E4M3 [heads][N][d].
+//   tiles key block kb of KV head g: the block's B x d values are rounded to E4M3
+//         into LDS [key][d] and written as the d x B tile with the keys in vt_key
+//         order, laid out by vt_offset (keys past N are zero).  A thread turns 4
+//         dimensions x 16 positions at a time in registers (positions 4 q .. 4 q +
+//         3 are consecutive keys); eight threads fill a 128-byte row.
+// HBM-bound: 40961 tokens, 32 / 4 heads, amax and packing 239 us in seven launches
+// -> 175 in three (197 with the heads in the order of the maximum's pass).
 template <int BS>
-__global__ __launch_bounds__(256) void fp8_pack_vt_kernel(const uint16_t* __restrict__ V, int64_t head_stride,
-                                                          int64_t tok_stride, int N, int M,
-                                                          const float* __restrict__ amax_v,
-                                                          uint8_t* __restrict__ V8t) {
-  __shared__ uint8_t tile[BS * kHeadDim];
-  const int kb = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
-  const float inv = fp8_inv_scale(amax_v[g]);
-  const int nk = min(BS, N - kb * BS);
-  const uint16_t* src = V + g * head_stride + (int64_t)kb * BS * tok_stride;
-  // BS rows x 16 chunks of 8 elements.
-  for (int c = tid; c < BS * 16; c += 256) {
-    const int key = c >> 4;
-    uint2 o = make_uint2(0u, 0u);
-    if (key < nk) {
-      float f[8];
-      unpack8(*reinterpret_cast<const uint4*>(src + key * tok_stride + 8 * (c & 15)), f);
-      o.x = (uint32_t)pack4_fp8(f[0] * inv, f[1] * inv, f[2] * inv, f[3] * inv);
-      o.y = (uint32_t)pack4_fp8(f[4] * inv, f[5] * inv, f[6] * inv, f[7] * inv);
+__global__ __launch_bounds__(256) void fp8_pack_kernel(const Fp8Inputs in, int M, int row_groups,
+                                                       const float* __restrict__ amax, uint8_t* __restrict__ Q8,
+                                                       uint8_t* __restrict__ K8, uint8_t* __restrict__ V8t) {
+  __shared__ uint32_t tile[BS * kVtRowWords];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= M * in.Hkv) {
+    const int w = blockIdx.x - M * in.Hkv;
+    const int head = in.Hq + in.Hkv - 1 - w / row_groups;
+    int64_t tok;
+    const uint16_t* rows = head_rows(in, head, &tok);
+    const int chunks = in.N * (kHeadDim / 8);
+    const int base = (row_groups - 1 - w % row_groups) * kPackChunks;
+    const float inv = fp8_inv_scale(amax[head]);
+    uint2* dst = reinterpret_cast<uint2*>(head < in.Hq ? Q8 : K8) +
+                 (size_t)(head < in.Hq ? head : head - in.Hq) * chunks;
+    uint4 v[kPackChunks / 256];
+#pragma unroll
+    for (int k = 0; k < kPackChunks / 256; ++k) v[k] = load_chunk(rows, tok, min(base + 256 * k + tid, chunks - 1));
+#pragma unroll
+    for (int k = 0; k < kPackChunks / 256; ++k) {
+      const int c = base + 256 * k + tid;
+      if (c < chunks) dst[c] = pack_chunk(v[k], inv);
     }
-    *reinterpret_cast<uint2*>(tile + 8 * c) = o;
+    return;
+  }
+  const int g = in.Hkv - 1 - blockIdx.x / M, kb = M - 1 - blockIdx.x % M;
+  const float inv = fp8_inv_scale(amax[in.Hq + in.Hkv + g]);
+  const int nk = min(BS, in.N - kb * BS);
+  const uint16_t* src = in.V + g * in.st.kv_head + (int64_t)kb * BS * in.st.kv_tok;
+  // BS rows x 16 chunks of 8 elements, up to eight loads in flight per thread.
+  constexpr int kSteps = BS * 16 / 256, kFlight = kSteps < 8 ? kSteps : 8;
+#pragma unroll 1
+  for (int k0 = 0; k0 < kSteps; k0 += kFlight) {
+    uint4 v[kFlight];
+#pragma unroll
+    for (int k = 0; k < kFlight; ++k) v[k] = load_chunk(src, in.st.kv_tok, min(256 * (k0 + k) + tid, 16 * nk - 1));
+#pragma unroll
+    for (int k = 0; k < kFlight; ++k) {
+      const int c = 256 * (k0 + k) + tid;
+      const uint2 o = c < 16 * nk ? pack_chunk(v[k], inv) : make_uint2(0u, 0u);
+      uint32_t* row = tile + (c >> 4) * kVtRowWords + 2 * (c & 15);
+      row[0] = o.x;
+      row[1] = o.y;
+    }
   }
   __syncthreads();
-  // d rows x BS/16 chunks of 16 positions.
   uint8_t* out = V8t + ((size_t)g * M + kb) * (size_t)kHeadDim * BS;
-  for (int c = tid; c < kHeadDim * (BS / 16); c += 256) {
-    const int d = c / (BS / 16), p0 = 16 * (c % (BS / 16));
-    uint32_t w[4];
+  constexpr int kPos = BS / 16;  // groups of 16 positions
+#pragma unroll 1
+  for (int t = tid; t < kHeadDim / 4 * kPos; t += 256) {
+    const int dg = t / kPos, p0 = 16 * (t % kPos);  // dimensions 4 dg .. + 3
+    uint32_t w[4][4];                               // [dimension][position / 4]
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      uint32_t x = 0u;
+      const uint32_t* k = tile + vt_key(p0 + 4 * q) * kVtRowWords + dg;
+      uint32_t x[4];
+      transpose4x4(k[0], k[kVtRowWords], k[2 * kVtRowWords], k[3 * kVtRowWords], x);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x |= (uint32_t)tile[vt_key(p0 + 4 * q + e) * kHeadDim + d] << (8 * e);
-      w[q] = x;
+      for (int e = 0; e < 4; ++e) w[e][q] = x[e];
     }
-    *reinterpret_cast<uint4*>(out + vt_offset<BS>(d, p0)) = make_uint4(w[0], w[1], w[2], w[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      *reinterpret_cast<uint4*>(out + vt_offset<BS>(4 * dg + e, p0)) = make_uint4(w[e][0], w[e][1], w[e][2], w[e][3]);
   }
 }
 
@@ -449,45 +524,45 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 hipError_t launch_fp8_amax(const uint16_t* Q, const uint16_t* K, const uint16_t* V, const Strides& st, int n_tokens,
                            int n_q_heads, int n_kv_heads, float* amax, hipStream_t s) {
-  const int n = n_q_heads + 2 * n_kv_heads;
+  const Fp8Inputs in{Q, K, V, st, n_tokens, n_q_heads, n_kv_heads};
+  const int heads = n_q_heads + 2 * n_kv_heads;
   uint32_t* bits = reinterpret_cast<uint32_t*>(amax);
-  hipLaunchKernelGGL(fp8_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, s, bits, n);
-  const int64_t chunks = (int64_t)n_tokens * kHeadDim / 8;
-  const int gx = (int)((chunks + 255) / 256 < 64 ? (chunks + 255) / 256 : 64);
-  hipLaunchKernelGGL(fp8_amax_kernel, dim3(gx, n_q_heads), dim3(256), 0, s, Q, st.q_head, st.q_tok, chunks, bits);
-  hipLaunchKernelGGL(fp8_amax_kernel, dim3(gx, n_kv_heads), dim3(256), 0, s, K, st.kv_head, st.kv_tok, chunks,
-                     bits + n_q_heads);
-  hipLaunchKernelGGL(fp8_amax_kernel, dim3(gx, n_kv_heads), dim3(256), 0, s, V, st.kv_head, st.kv_tok, chunks,
-                     bits + n_q_heads + n_kv_heads);
+  // Workgroups per head: about 1024 in all.  Their atomics share a cache line and
+  // cost ~10 ns each (amax and packing of 10000 tokens, 32 / 4 heads: 80 us with
+  // 8192, 61 with 4096, 49 with 2048, 42 with 1024; 40961 tokens 203, 186, 176,
+  // 175).  A short head is one workgroup's: no counters to clear.
+  const int steps = (n_tokens * (kHeadDim / 8) + kAmaxStep - 1) / kAmaxStep;
+  int slices = 1024 / heads > 1 ? 1024 / heads : 1;
+  slices = slices < steps ? slices : steps;
+  if (steps <= kAmaxOneSteps) slices = 1;
+  if (slices > 1) {
+    hipLaunchKernelGGL(fp8_zero_kernel, dim3((heads + 255) / 256), dim3(256), 0, s, bits, heads);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fp8_amax_kernel, dim3(slices, heads), dim3(256), 0, s, in, bits);
+  return hipGetLastError();
+}
+
+template <int BS>
+static hipError_t launch_fp8_pack_bs(const Fp8Inputs& in, int n_blocks, const float* amax, uint8_t* Q8, uint8_t* K8,
+                                     uint8_t* V8t, hipStream_t s) {
+  const int row_groups = (in.N * (kHeadDim / 8) + kPackChunks - 1) / kPackChunks;
+  const unsigned grid = (unsigned)n_blocks * in.Hkv + (unsigned)row_groups * (in.Hq + in.Hkv);
+  hipLaunchKernelGGL(fp8_pack_kernel<BS>, dim3(grid), dim3(256), 0, s, in, n_blocks, row_groups, amax, Q8, K8, V8t);
   return hipGetLastError();
 }
 
 hipError_t launch_fp8_pack(const uint16_t* Q, const uint16_t* K, const uint16_t* V, const Strides& st, int n_tokens,
                            int n_q_heads, int n_kv_heads, int block_size, int n_blocks, const float* amax, uint8_t* Q8,
                            uint8_t* K8, uint8_t* V8t, hipStream_t s) {
-  const int64_t chunks = (int64_t)n_tokens * kHeadDim / 8;
-  const int gx = (int)((chunks + 255) / 256 < 512 ? (chunks + 255) / 256 : 512);
-  hipLaunchKernelGGL(fp8_pack_rows_kernel, dim3(gx, n_q_heads), dim3(256), 0, s, Q, st.q_head, st.q_tok, chunks,
-                     amax, Q8);
-  hipLaunchKernelGGL(fp8_pack_rows_kernel, dim3(gx, n_kv_heads), dim3(256), 0, s, K, st.kv_head, st.kv_tok, chunks,
-                     amax + n_q_heads, K8);
-  const float* amax_v = amax + n_q_heads + n_kv_heads;
+  const Fp8Inputs in{Q, K, V, st, n_tokens, n_q_heads, n_kv_heads};
   switch (block_size) {
-    case 64:
-      hipLaunchKernelGGL(fp8_pack_vt_kernel<64>, dim3(n_blocks, n_kv_heads), dim3(256), 0, s, V, st.kv_head,
-                         st.kv_tok, n_tokens, n_blocks, amax_v, V8t);
-      break;
-    case 128:
-      hipLaunchKernelGGL(fp8_pack_vt_kernel<128>, dim3(n_blocks, n_kv_heads), dim3(256), 0, s, V, st.kv_head,
-                         st.kv_tok, n_tokens, n_blocks, amax_v, V8t);
-      break;
-    case 256:
-      hipLaunchKernelGGL(fp8_pack_vt_kernel<256>, dim3(n_blocks, n_kv_heads), dim3(256), 0, s, V, st.kv_head,
-                         st.kv_tok, n_tokens, n_blocks, amax_v, V8t);
-      break;
+    case 64: return launch_fp8_pack_bs<64>(in, n_blocks, amax, Q8, K8, V8t, s);
+    case 128: return launch_fp8_pack_bs<128>(in, n_blocks, amax, Q8, K8, V8t, s);
+    case 256: return launch_fp8_pack_bs<256>(in, n_blocks, amax, Q8, K8, V8t, s);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <int BS>

@@ -100,6 +100,26 @@ def _check_pack(r, ref, w):
             assert np.array_equal(vt[g, b], _vt_layout(want[keys].T, B)), f"V^T tile ({g}, {b})"
 
 
+@pytest.mark.parametrize("n", [1, 65, 1024, 1025, 2600])
+@pytest.mark.parametrize("B,heads", [(64, (3, 3)), (128, (2, 1)), (256, (4, 2))])
+def test_fp8_packing_edges(n, B, heads):
+    """Packing alone at the edges of its split: one workgroup per head (up to
+    1024 tokens) and several, partial steps, partial tiles; amax and every code
+    bit-exact.  A stale amax does not matter."""
+    import torch
+    import paper_2609_20971_amd as rbs
+    w = WORKLOADS["tiny-2k"].with_(name="fp8-pack", seq_len=n, n_q_heads=heads[0], n_kv_heads=heads[1], block_size=B,
+                                   needles_per_kv_head=0, seed=90 + n)
+    _say(f"[fp8] packing N={n} heads={heads} B={B}")
+    inp = make_inputs(w)
+    shape = rbs.make_shape(n, *heads, B)
+    f8 = rbs.allocate_fp8(shape)
+    f8.amax.fill_(3.0e38)
+    rbs.rbs_fp8_prepare(shape, *(H.to_device(inp[x]) for x in ("q", "k", "v")), f8)
+    torch.cuda.synchronize()
+    _check_pack(dict(f8=f8), _oracle_fp8(inp), w)
+
+
 def _bound(Qh, Kg, Vg, B, i, ids, O_ref, scale):
     """Per-element tolerance of one query block (derivation in the module doc):
     (2u/(1-u) + 2(e^{2 D} - 1)) * sum_j w_j |v_j - O| + ACC (sum_j w_j |v_j| + |O|)

@@ -7,7 +7,7 @@
 // centroid), plus the select-ready f16 copy of the centroid.
 //
 // quantile_kernel: one workgroup per KV head finds the head's 0.5 / 0.9 radius
-// quantiles with an in-LDS radix select over its M radii (order_stats4) and writes beta and
+// quantiles with an in-LDS histogram over its M radii and writes beta and
 // the select-ready uplift of every block.  It is a separate launch because a
 // device-wide "last workgroup" hand-off would need an agent-scope release per
 // workgroup, which on a multi-XCD gfx950 writes back the whole L2 each time.
@@ -17,129 +17,16 @@
 namespace rbs {
 
 constexpr int kStatsThreads = 256;
-constexpr int kMaxBlocks = 4096;
+constexpr int kMaxBlocks = 4096;  // T PER of the largest quantile_kernel
 
-// Values of the order statistics of ranks ka, ka + 1, kb and kb + 1 (0-based;
-// a rank past n - 1 takes the value of rank n - 1) of n non-negative floats
-// held as their uint32 bit patterns in LDS.  Non-negative IEEE floats order
-// like their bit patterns, so an MSB-first radix select finds a rank digit by
-// digit.  The bits that every key shares (radii of one head mostly share their
-// exponent) are found first with an AND / OR reduction and skipped; the
-// remaining bits are taken in digits of up to 8, each wave counting its keys
-// in a histogram of its own (fewer colliding LDS atomics); ranks ka + 1 and
-// kb + 1 then follow from one count-and-minimum pass.
-__device__ void order_stats4(const uint32_t* keys, int n, int ka, int kb, uint32_t* hist /*4 waves x 2 x 256*/,
-                             uint32_t* red /*8*/, uint32_t* prefix /*2*/, int* remaining /*2*/,
-                             uint32_t* out /*4*/) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t a = 0xffffffffu, o = 0u;
-  for (int e = tid; e < n; e += kStatsThreads) {
-    a &= keys[e];
-    o |= keys[e];
-  }
+// Maximum / minimum of x over the 64 lanes, in every lane.
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
-    a &= (uint32_t)__shfl_xor((int)a, off, kWave);
-    o |= (uint32_t)__shfl_xor((int)o, off, kWave);
+    const uint32_t y = (uint32_t)__shfl_xor((int)x, off, kWave);
+    x = y > x ? y : x;
   }
-  if (lane == 0) {
-    red[wave] = a;
-    red[4 + wave] = o;
-  }
-  __syncthreads();
-  a = red[0] & red[1] & red[2] & red[3];
-  o = red[4] | red[5] | red[6] | red[7];
-  const uint32_t diff = a ^ o;
-  int bits = diff == 0u ? 0 : 32 - __clz((int)diff);  // the low bits that differ between keys
-  if (tid < 2) {
-    prefix[tid] = bits >= 32 ? 0u : (a >> bits) << bits;  // the shared high bits
-    remaining[tid] = tid == 0 ? ka : kb;
-  }
-  while (bits > 0) {
-    const int width = bits >= 8 ? 8 : bits;
-    const int shift = bits - width;
-    const uint32_t hi_mask = bits >= 32 ? 0u : (0xffffffffu << bits);
-    const uint32_t digit_mask = (1u << width) - 1u;
-    for (int e = tid; e < 4 * 2 * 256; e += kStatsThreads) hist[e] = 0u;
-    __syncthreads();
-    const uint32_t p0 = prefix[0], p1 = prefix[1];
-    uint32_t* own = hist + wave * 2 * 256;
-    for (int e = tid; e < n; e += kStatsThreads) {
-      const uint32_t x = keys[e];
-      const uint32_t hx = x & hi_mask, digit = (x >> shift) & digit_mask;
-      if (hx == p0) atomicAdd(&own[digit], 1u);
-      if (hx == p1) atomicAdd(&own[256 + digit], 1u);
-    }
-    __syncthreads();
-    if (wave < 2) {
-      int c[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int bin = wave * 256 + 4 * lane + j;
-        c[j] = (int)(hist[bin] + hist[2 * 256 + bin] + hist[4 * 256 + bin] + hist[6 * 256 + bin]);
-      }
-      const int own_count = c[0] + c[1] + c[2] + c[3];
-      int incl = own_count;
-      for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += v;
-      }
-      const int excl = incl - own_count;
-      const int k = remaining[wave];
-      if (excl <= k && k < incl) {
-        int kr = k - excl, digit = 4 * lane;
-        if (kr >= c[0]) { kr -= c[0]; ++digit;
-          if (kr >= c[1]) { kr -= c[1]; ++digit;
-            if (kr >= c[2]) { kr -= c[2]; ++digit; } } }
-        prefix[wave] |= (uint32_t)digit << shift;
-        remaining[wave] = kr;
-      }
-    }
-    __syncthreads();  // the histograms are read and the prefixes written before the next digit
-    bits -= width;
-  }
-  __syncthreads();
-  // Rank k + 1: the same value when more than k + 1 keys are <= it, else the
-  // smallest key above it.
-  const uint32_t xa = prefix[0], xb = prefix[1];
-  uint32_t na = 0u, nb = 0u, ma = 0xffffffffu, mb = 0xffffffffu;
-  for (int e = tid; e < n; e += kStatsThreads) {
-    const uint32_t x = keys[e];
-    na += x <= xa ? 1u : 0u;
-    nb += x <= xb ? 1u : 0u;
-    if (x > xa) ma = x < ma ? x : ma;
-    if (x > xb) mb = x < mb ? x : mb;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    na += (uint32_t)__shfl_xor((int)na, off, kWave);
-    nb += (uint32_t)__shfl_xor((int)nb, off, kWave);
-    const uint32_t ya = (uint32_t)__shfl_xor((int)ma, off, kWave), yb = (uint32_t)__shfl_xor((int)mb, off, kWave);
-    ma = ya < ma ? ya : ma;
-    mb = yb < mb ? yb : mb;
-  }
-  __syncthreads();  // every wave is done reading red and prefix above
-  if (lane == 0) {
-    red[wave] = na + (nb << 16);  // n <= 4096: both counts fit in 16 bits
-    red[4 + wave] = 0u;
-    hist[wave] = ma;
-    hist[4 + wave] = mb;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t cnt = 0u, mina = 0xffffffffu, minb = 0xffffffffu;
-    for (int w = 0; w < 4; ++w) {
-      cnt += red[w];
-      mina = hist[w] < mina ? hist[w] : mina;
-      minb = hist[4 + w] < minb ? hist[4 + w] : minb;
-    }
-    const int ca = (int)(cnt & 0xffffu), cb = (int)(cnt >> 16);
-    out[0] = xa;
-    out[1] = (ka + 1 > n - 1 || ca >= ka + 2) ? xa : mina;
-    out[2] = xb;
-    out[3] = (kb + 1 > n - 1 || cb >= kb + 2) ? xb : minb;
-  }
-  __syncthreads();
+  return x;
 }
 
 // Block blockIdx.x of all the sequences' blocks (sequence s owns blocks
@@ -323,44 +210,147 @@ __global__ __launch_bounds__(kStatsThreads) void box_kernel(const uint16_t* __re
 }
 
 // KV head blockIdx.x of sequence blockIdx.y: the quantiles of that sequence's
-// radii (its own prompt's distribution).
-__global__ __launch_bounds__(kStatsThreads) void quantile_kernel(const float* __restrict__ radii, const SeqTable t,
-                                                                float* __restrict__ beta,
-                                                                float* __restrict__ quantiles,
-                                                                float* __restrict__ uplift, float sel_scale) {
-  __shared__ uint32_t keys[kMaxBlocks];
-  __shared__ uint32_t hist[4 * 2 * 256];
-  __shared__ uint32_t sel_red[8];
-  __shared__ uint32_t sel_prefix[2];
-  __shared__ int sel_remaining[2];
-  __shared__ uint32_t sel_out[4];
-  const int g = blockIdx.x, sq = blockIdx.y, tid = threadIdx.x;
+// radii (its own prompt's distribution), by T threads holding PER radii each.
+//
+// The four order statistics wanted (ranks ka, ka + 1, kb, kb + 1; 0-based, a rank
+// past M - 1 taken as M - 1) are found from one histogram: non-negative IEEE
+// floats order like their bit patterns, so (bits - min) >> shift is a monotone
+// map onto kBins bins; the keys of each wanted rank's bin (a few) are listed by
+// their offset in it, and one wave per rank finds the value among them by bitwise
+// bisection with ballots (any number of keys, so any distribution).
+// Latency-bound, one workgroup per head: a chain of seven barriers (the 8-bit
+// radix passes that it replaces took some twenty).  Kernel time at M = 32, 256,
+// 1024, 2048, 4096: 5.6, 7.0, 8.8, 12.2, 20.4 -> 5.0, 6.1, 6.1, 7.0, 7.6 us.
+constexpr int kBins = 1024;
+
+template <int T, int PER>
+__global__ __launch_bounds__(T) void quantile_kernel(const float* __restrict__ radii, const SeqTable t,
+                                                     float* __restrict__ beta, float* __restrict__ quantiles,
+                                                     float* __restrict__ uplift, float sel_scale) {
+  constexpr int NW = T / kWave;
+  constexpr int kBinsPer = kBins / T;  // bins of a thread's share of the scan
+  __shared__ uint32_t hist[kBins];
+  __shared__ uint32_t list[4][T * PER];  // keys of each wanted rank's bin
+  __shared__ uint32_t red[2][NW];
+  __shared__ uint32_t wave_sum[NW];
+  __shared__ uint32_t bin_of[4], below[4], listed[4];  // per rank: its bin, keys below the bin, keys listed
+  __shared__ float order[4];
+  const int g = blockIdx.x, sq = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int M = t.blk[sq + 1] - t.blk[sq];
   const size_t base = (size_t)g * t.blk[t.n] + t.blk[sq];
   const float* rg_radii = radii + base;
-  for (int e = tid; e < M; e += kStatsThreads) keys[e] = __float_as_uint(rg_radii[e]);
+
+  // Keys (the last one again past the end), their range.
+  uint32_t key[PER];
+  uint32_t hi = 0u, lo_inv = 0u;  // max of bits, max of ~bits
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    key[k] = __float_as_uint(rg_radii[min(tid + k * T, M - 1)]);
+    hi = key[k] > hi ? key[k] : hi;
+    lo_inv = ~key[k] > lo_inv ? ~key[k] : lo_inv;
+  }
+#pragma unroll
+  for (int k = 0; k < kBinsPer; ++k) hist[tid + k * T] = 0u;
+  if (tid < 4) listed[tid] = 0u;
+  hi = wave_max_u(hi);
+  lo_inv = wave_max_u(lo_inv);
+  if (lane == 0) {
+    red[0][wave] = hi;
+    red[1][wave] = lo_inv;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    hi = red[0][w] > hi ? red[0][w] : hi;
+    lo_inv = red[1][w] > lo_inv ? red[1][w] : lo_inv;
+  }
+  const uint32_t lo = ~lo_inv, range = hi - lo;
+  const int shift = range < (uint32_t)kBins ? 0 : 22 - __clz((int)range);  // range >> shift < 1024
+
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (tid + k * T < M) atomicAdd(&hist[(key[k] - lo) >> shift], 1u);
   __syncthreads();
 
-  // Linear interpolation between order statistics: h = (M - 1) p, done in
-  // integers so the ranks are exact.
+  // Exclusive scan over the bins (thread tid: bins kBinsPer tid ..) and, in the
+  // bin that holds it, each wanted rank.  Linear interpolation between order
+  // statistics: h = (M - 1) p, done in integers so the ranks are exact.
   const int n1 = M - 1;
   const int k50 = n1 / 2, k90 = (9 * n1) / 10;
+  const uint32_t rank[4] = {(uint32_t)k50, (uint32_t)min(k50 + 1, n1), (uint32_t)k90, (uint32_t)min(k90 + 1, n1)};
+  uint32_t c[kBinsPer], own = 0u;
+#pragma unroll
+  for (int k = 0; k < kBinsPer; ++k) {
+    c[k] = hist[kBinsPer * tid + k];
+    own += c[k];
+  }
+  uint32_t incl = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t v = (uint32_t)__shfl_up((int)incl, off, kWave);
+    if (lane >= off) incl += v;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  uint32_t excl = incl - own;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) excl += w < wave ? wave_sum[w] : 0u;
+#pragma unroll
+  for (int k = 0; k < kBinsPer; ++k) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (excl <= rank[r] && rank[r] < excl + c[k]) {
+        bin_of[r] = (uint32_t)(kBinsPer * tid + k);
+        below[r] = excl;
+      }
+    excl += c[k];
+  }
+  __syncthreads();
+
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const uint32_t bin = (key[k] - lo) >> shift;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (tid + k * T < M && bin == bin_of[r])
+        list[r][atomicAdd(&listed[r], 1u)] = key[k] - lo - (bin << shift);
+  }
+  __syncthreads();
+  // Wave r: the value of rank (rank[r] - below[r]) among its list -- the largest v
+  // such that no more keys than that lie below it.
+  if (wave < 4) {
+    const uint32_t n = listed[wave], want = rank[wave] - below[wave];
+    const uint32_t mine = list[wave][(uint32_t)lane < n ? lane : 0];
+    uint32_t v = 0u;
+    for (int bit = shift - 1; bit >= 0; --bit) {
+      const uint32_t probe = v | (1u << bit);
+      uint32_t less = (uint32_t)__popcll(__ballot((uint32_t)lane < n && mine < probe));
+      for (uint32_t e = kWave + lane; e - lane < n; e += kWave)
+        less += (uint32_t)__popcll(__ballot(e < n && list[wave][e < n ? e : 0] < probe));
+      if (less <= want) v = probe;
+    }
+    v += lo + (bin_of[wave] << shift);
+    if (lane == 0) order[wave] = __uint_as_float(v);
+  }
+  __syncthreads();
+
   const float f50 = (n1 % 2) ? 0.5f : 0.0f;
   const float f90 = (float)((9 * n1) % 10) / 10.0f;
-  order_stats4(keys, M, k50, k90, hist, sel_red, sel_prefix, sel_remaining, sel_out);
-  const float x50 = __uint_as_float(sel_out[0]), x50b = __uint_as_float(sel_out[1]);
-  const float x90 = __uint_as_float(sel_out[2]), x90b = __uint_as_float(sel_out[3]);
-  const float r_low = x50 + f50 * (x50b - x50);
-  const float r_high = x90 + f90 * (x90b - x90);
+  const float r_low = order[0] + f50 * (order[1] - order[0]);
+  const float r_high = order[2] + f90 * (order[3] - order[2]);
   const bool spread = r_high > r_low;
   const float span = r_high - r_low;
-  for (int e = tid; e < M; e += kStatsThreads) {
-    const float r = __uint_as_float(keys[e]);
-    float bt;
-    if (spread) bt = fminf(fmaxf((r - r_low) / span, 0.0f), 1.0f);
-    else bt = r > r_low ? 1.0f : 0.0f;
-    beta[base + e] = bt;
-    uplift[base + e] = r * bt * sel_scale;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int e = tid + k * T;
+    if (e < M) {
+      const float r = __uint_as_float(key[k]);
+      float bt;
+      if (spread) bt = fminf(fmaxf((r - r_low) / span, 0.0f), 1.0f);
+      else bt = r > r_low ? 1.0f : 0.0f;
+      beta[base + e] = bt;
+      uplift[base + e] = r * bt * sel_scale;
+    }
   }
   if (tid == 0) {
     const size_t q = (size_t)sq * gridDim.x + g;
@@ -432,8 +422,16 @@ hipError_t launch_stats_varlen(const StatsArgs& a, const SeqTable& t, hipStream_
 #undef RBS_STATS_CASE
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(quantile_kernel, dim3(a.n_kv_heads, t.n), dim3(kStatsThreads), 0, s, a.radii, t, a.beta,
-                     a.quantiles, a.uplift, sel_scale);
+  int m_max = 0;
+  for (int q = 0; q < t.n; ++q) m_max = t.blk[q + 1] - t.blk[q] > m_max ? t.blk[q + 1] - t.blk[q] : m_max;
+  const dim3 heads(a.n_kv_heads, t.n);
+#define RBS_QUANTILE(T, PER)                                                                            \
+  hipLaunchKernelGGL((quantile_kernel<T, PER>), heads, dim3(T), 0, s, a.radii, t, a.beta, a.quantiles, \
+                     a.uplift, sel_scale)
+  if (m_max <= 256) RBS_QUANTILE(256, 1);
+  else if (m_max <= 1024) RBS_QUANTILE(1024, 1);
+  else RBS_QUANTILE(1024, 4);
+#undef RBS_QUANTILE
   return hipGetLastError();
 }
 

@@ -170,6 +170,34 @@ def test_threshold_and_forced_variants(tau, forced):
         assert (counts == np.arange(w.n_blocks)[None, :] + 1).all()
 
 
+@pytest.mark.parametrize("blocks", [1, 2, 3, 11, 255, 256, 257, 1024, 1025, 4096])
+@pytest.mark.parametrize("kind", ["spread", "few_values", "outliers"])
+def test_radius_quantiles(blocks, kind):
+    """The radius quantiles against the same order statistics of the radii that
+    the call wrote (exact: they are selected, and interpolated in fp32)."""
+    import torch
+    import paper_2609_20971_amd as rbs
+    rng = np.random.default_rng(blocks)
+    scale = {"spread": np.exp(0.5 * rng.standard_normal((2, blocks))),
+             "few_values": rng.integers(1, 4, (2, blocks)).astype(np.float64),
+             "outliers": np.exp(12.0 * rng.standard_normal((2, blocks)))}[kind]
+    n = 64 * blocks - 63 if blocks > 1 else 64          # a last block of one token: radius 0
+    x = rng.standard_normal((2, 64, 128), dtype=np.float32)
+    k = (x[:, None] * scale[:, :, None, None].astype(np.float32)).reshape(2, blocks * 64, 128)[:, :n]
+    K = torch.from_numpy(np.ascontiguousarray(k)).to(torch.bfloat16).cuda()
+    st = rbs.rbs_block_stats(rbs.make_shape(n, 2, 2, 64), K)
+    torch.cuda.synchronize()
+    radii, got = st.radii.cpu().numpy(), st.quantiles.cpu().numpy()
+    for g in range(2):
+        r = np.sort(radii[g])
+        for col, (num, den) in enumerate(((1, 2), (9, 10))):
+            h, rem = divmod(num * (blocks - 1), den)
+            lo, hi = r[h], r[min(h + 1, blocks - 1)]
+            want = np.float32(lo) + np.float32(rem / den) * (hi - lo)
+            # (a fused multiply-add may round the interpolation once less)
+            assert abs(got[g, col] - want) <= np.spacing(np.float32(max(abs(want), lo))), (g, col, got[g, col], want)
+
+
 def test_degenerate_radii_and_zero_queries():
     """Identical key blocks (r_high == r_low) and all-zero query rows."""
     w = WORKLOADS["tiny-2k"].with_(seq_len=1024, seed=8)

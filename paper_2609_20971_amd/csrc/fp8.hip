@@ -12,8 +12,8 @@
 //   attn_fp8      per (query head, query block), B = 64, 128 or 256, the
 //                 orientation and pipeline of the bf16 kernel: S^T = K Q^T and
 //                 O^T = V^T P^T, Q in registers, K and V^T tiles copied
-//                 global -> LDS (B x 128 bytes each, 128-byte rows, 16-byte
-//                 chunks XOR-swizzled), online softmax in fp32 in steps of up
+//                 global -> LDS (B x 128 bytes each, two of each, 128-byte rows,
+//                 16-byte chunks XOR-swizzled), online softmax in fp32 in steps of up
 //                 to 128 keys, P rounded to E4M3.
 //                 The softmax denominator is accumulated by the matrix core
 //                 too (ones times P^T), from exactly the rounded P.  Bound by
@@ -22,7 +22,9 @@
 //                 cycles).  40961 tokens, 32 / 4 heads, partly shared lists:
 //                 B = 128 1911 us; with the denominator on 16x16x128 ops 1850;
 //                 with the lists read through scalar loads (a vector load's
-//                 wait held every block until its tile copies had landed) 1773.
+//                 wait held every block until its tile copies had landed) 1773;
+//                 with two K and two V tiles and one barrier per block instead
+//                 of four 1650 (V's copies issued after QK^T: 1730).
 //
 // Dequantisation: amax / 448 per head, folded into the logit scale (q, k) and
 // the output normalisation (v).
@@ -315,8 +317,11 @@ __device__ __forceinline__ i32x8 read_vt32(const unsigned char* v_lds, int kbase
 }
 
 // Query block i of query head h; counts and indices come as restricted pointers
-// so that the list is read by scalar loads; k_lds, v_lds: BS * 128 bytes each.  The
-// block's keys are taken in softmax steps of up to 128 (two for B = 256).
+// so that the list is read by scalar loads; k_lds, v_lds: two tiles of BS * 128
+// bytes each, so that a block's copies have the block before it to land and one
+// barrier per block is left (FP8 tiles are half the bf16 ones: the doubled tiles
+// still leave the compute unit its two workgroups at B = 128).  The block's keys
+// are taken in softmax steps of up to 128 (two for B = 256).
 // last_block(): called by every wave as the last listed block begins.
 template <int BS, typename LastBlock>
 __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int32_t* __restrict__ counts,
@@ -387,9 +392,18 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int3
     const int nk = min(BS, N - kb * BS);
     const bool diag = kb == i;
 
-    RBS_WAIT_VMCNT(4);  // this block's K has landed (its V may still be in flight)
+    // This block's tiles have landed, and every wave is done with the previous
+    // block's, which the next block's copies overwrite.
+    RBS_WAIT_VMCNT(0);
     __syncthreads();
     if (!has_next) last_block();
+    const unsigned char* k_tile = k_lds + (n & 1) * BS * 128;
+    const unsigned char* v_tile = v_lds + (n & 1) * BS * 128;
+    const uint32_t next_buf = (uint32_t)((n + 1) & 1) * BS * 128;
+    if (has_next) {
+      issue_tile8(kg + (size_t)kb_next * BS * kHeadDim, min(BS, N - kb_next * BS), k_base + next_buf, wave, lane);
+      issue_tile8(vg + (size_t)kb_next * kHeadDim * BS, BS, v_base + next_buf, wave, lane);
+    }
 
     // (Steps not unrolled: two unrolled 128-key steps spill heavily.)
 #pragma unroll 1
@@ -401,12 +415,7 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int3
         s[mt] = f32x16{};
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
-          s[mt] = mfma_f8(read_row32(k_lds, kbase + 32 * mt + l32, 2 * ks + half), qreg[ks], s[mt]);
-      }
-      if (sub == BS / SUB - 1) {
-        __syncthreads();  // every wave is done with this K tile
-        if (has_next)
-          issue_tile8(kg + (size_t)kb_next * BS * kHeadDim, min(BS, N - kb_next * BS), k_base, wave, lane);
+          s[mt] = mfma_f8(read_row32(k_tile, kbase + 32 * mt + l32, 2 * ks + half), qreg[ks], s[mt]);
       }
       if (diag || nk < BS) {
         // Keys past the block's end, and on the diagonal past the query.  The
@@ -451,22 +460,14 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int3
           pk[st][j] = pack4_fp8(fast_exp2(fmaf(s[t][r0], sl, -shift)), fast_exp2(fmaf(s[t][r0 + 1], sl, -shift)),
                                 fast_exp2(fmaf(s[t][r0 + 2], sl, -shift)), fast_exp2(fmaf(s[t][r0 + 3], sl, -shift)));
         }
-      if (sub == 0) {
-        // This block's V has landed.  The next block's K copies are already
-        // in flight behind it only when the block has a single step.
-        if (has_next && BS / SUB == 1) RBS_WAIT_VMCNT(4); else RBS_WAIT_VMCNT(0);
-        __syncthreads();
-      }
 #pragma unroll
       for (int st = 0; st < NST; ++st) {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt)
-          o[dt] = mfma_f8(read_vt32<BS>(v_lds, kbase, 32 * dt + l32, st, half), pk[st], o[dt]);
+          o[dt] = mfma_f8(read_vt32<BS>(v_tile, kbase, 32 * dt + l32, st, half), pk[st], o[dt]);
         lacc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(lsel, pk[st], lacc, 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
       }
     }
-    __syncthreads();  // every wave is done with this V tile
-    if (has_next) issue_tile8(vg + (size_t)kb_next * kHeadDim * BS, BS, v_base, wave, lane);
     kb = kb_next;
   }
 
@@ -495,8 +496,8 @@ __device__ __forceinline__ void attend_block_fp8(const AttnF8Args& c, const int3
 template <int BS>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_kernel(
     AttnF8Args c, const int32_t* __restrict__ counts, const int32_t* __restrict__ indices) {
-  __shared__ __align__(1024) unsigned char k_lds[BS * 128];
-  __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
+  __shared__ __align__(1024) unsigned char k_lds[2 * BS * 128];
+  __shared__ __align__(1024) unsigned char v_lds[2 * kHeadDim * BS];
   int h, i;
   work_of(blockIdx.x, gridDim.x, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
   attend_block_fp8<BS>(c, counts, indices, h, i, k_lds, v_lds, [] {});
@@ -507,8 +508,8 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 template <int BS>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fp8_queue_kernel(
     AttnF8Args c, const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, int* __restrict__ queue) {
-  __shared__ __align__(1024) unsigned char k_lds[BS * 128];
-  __shared__ __align__(1024) unsigned char v_lds[kHeadDim * BS];
+  __shared__ __align__(1024) unsigned char k_lds[2 * BS * 128];
+  __shared__ __align__(1024) unsigned char v_lds[2 * kHeadDim * BS];
   __shared__ int lds_slot;
   const int total = c.M * c.Hq;
   QueueTicket ticket(queue);

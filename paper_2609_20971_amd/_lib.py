@@ -221,13 +221,12 @@ def make_shape(n_tokens: int, n_q_heads: int, n_kv_heads: int, block_size: int, 
 # one GPU.  Q/K/V/O strides go into the rbs_shape passed on.  A mismatch
 # raises ValueError; nothing is launched.
 
-def _device_index(t) -> int:
-    if t.device.type != "cuda":
-        return -1
-    return t.device.index if t.device.index is not None else torch.cuda.current_device()
-
-
 def _check_tensor(name: str, t, dtype, sizes, contiguous=True):
+    # A small call's time is the host's, most of it in these checks: one pass
+    # over the cheap attributes, and the message only where one fails.
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == sizes
+            and (not contiguous or t.is_contiguous()) and t.stride(-1) == 1):
+        return
     if not isinstance(t, torch.Tensor):
         raise ValueError(f"{name} must be a torch.Tensor, not {type(t).__name__}")
     if t.dtype != dtype:
@@ -246,12 +245,13 @@ def _on_gpu(*named) -> int:
     for name, t in named:
         if t is None:
             continue
-        if t.device.type != "cuda":
+        if not t.is_cuda:
             raise ValueError(f"{name} must be on a GPU, not {t.device}")
+        index = t.get_device()
         if dev is None:
-            dev = _device_index(t)
-        elif _device_index(t) != dev:
-            raise ValueError(f"{name} is on cuda:{_device_index(t)}, the other arguments on cuda:{dev}")
+            dev = index
+        elif index != dev:
+            raise ValueError(f"{name} is on cuda:{index}, the other arguments on cuda:{dev}")
     return dev
 
 
@@ -259,22 +259,28 @@ def _heads_tokens(name: str, t, n_heads: int, n_tokens: int, head_dim: int):
     """A bf16 (head, token, dimension) tensor of any strides with a contiguous
     last dimension; returns its (head stride, token stride)."""
     _check_tensor(name, t, torch.bfloat16, (n_heads, n_tokens, head_dim), contiguous=False)
-    return t.stride(0), t.stride(1)
+    return t.stride()[:2]
 
 
 def _with_strides(shape: rbs_shape, q=None, kv=None) -> rbs_shape:
     """A copy of shape with the Q and/or K, V strides of the given tensors.
     Strides already set in shape must agree with the tensors'."""
     out = rbs_shape.from_buffer_copy(shape)
-    for pair, fields in ((q, ("q_stride_head", "q_stride_tok")), (kv, ("kv_stride_head", "kv_stride_tok"))):
-        if pair is None:
-            continue
-        for value, field in zip(pair, fields):
-            given = getattr(shape, field)
-            if given not in (0, value):
-                raise ValueError(f"shape.{field} = {given} disagrees with the tensor's stride {value}")
-            setattr(out, field, value)
+    if q is not None:
+        _set_stride(out, "q_stride_head", q[0])
+        _set_stride(out, "q_stride_tok", q[1])
+    if kv is not None:
+        _set_stride(out, "kv_stride_head", kv[0])
+        _set_stride(out, "kv_stride_tok", kv[1])
     return out
+
+
+def _set_stride(shape: rbs_shape, field: str, value: int):
+    given = getattr(shape, field)
+    if given != value:
+        if given != 0:
+            raise ValueError(f"shape.{field} = {given} disagrees with the tensor's stride {value}")
+        setattr(shape, field, value)
 
 
 def _check_q(shape: rbs_shape, Q):

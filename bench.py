@@ -360,7 +360,7 @@ def main():
         _log(f"[bench] with a {args.flush_gib} GiB read between steps: stats {fms[0]:.3f} ms, "
              f"select {fms[1]:.3f} ms, attention {fms[2]:.3f} ms")
 
-    # The fused entry point over the same steps (same results, one pass).
+    # The select-attend entry point over the same steps (same results, one call).
     fused_ms = None
     if args.fused_steps > 0:
         fcounts, findices = rbs.allocate_lists(shape, dev)

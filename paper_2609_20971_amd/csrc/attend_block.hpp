@@ -1,6 +1,6 @@
 // Stage 3 device code: causal GQA block-sparse attention of one query block
-// (Sec. 3.3; Algorithm 1, last step), shared by the stand-alone attention
-// kernel and the fused select-then-attend kernel.
+// (Sec. 3.3; Algorithm 1, last step), shared by the single-sequence and the
+// batch kernels.
 //
 // One workgroup per (query head, query block); wave w owns 32 query tokens.
 // The kernel works in the transposed orientation so that every lane owns one
@@ -135,7 +135,7 @@ constexpr float kLazyRescaleAt = 4294967296.0f;
 // weight under 2^-62).
 constexpr float kRefMargin = 64.0f;
 
-// Arguments of one attention pass, shared by the stand-alone and the fused kernel.
+// Arguments of one attention pass.
 struct AttnCore {
   const uint16_t* Q;
   const uint16_t* K;
@@ -513,10 +513,9 @@ __device__ __forceinline__ void work_of(int id, int total, int M, int hq, int gr
 // same order, but a workgroup takes its next slot as soon as it is free
 // instead of waiting for the in-order dispatcher, which holds back every XCD
 // while one of them has no free slot.  Once its own queue is empty, a
-// workgroup takes the remaining slots of the other queues in turn (queue
-// j % 8 + 1, + 2, ... modulo 8), so that the XCDs that run faster share the
-// tail of the slower ones.  kQueueInts int32 counters, zeroed by reset_queues
-// before each launch.
+// workgroup takes the remaining slots of the other queues (the next one with a
+// slot left, cyclically), so that the XCDs that run faster share the tail of the
+// slower ones.  The counters are set by reset_queues before each launch.
 
 // A workgroup's place in the queues: the queue it takes tickets from, and its
 // next ticket of that queue (wave 0's lanes; valid when `taken`).

@@ -49,21 +49,6 @@ __device__ __forceinline__ int xcd_remap(int id, int total) {
   return ((s >> 3) << 6) + (x << 3) + (s & 7);
 }
 
-// One 16-byte-per-lane global -> LDS copy: lane l's 16 bytes from
-// gbase + voff land at LDS byte lds_addr + 16 l.  Issued from inline assembly
-// so that the compiler's wait-count pass does not treat every later LDS read as
-// dependent on it (it would wait for all outstanding copies); the kernel waits
-// for the copies it needs with explicit vmcnt counts instead.  Later-issued
-// vector loads only make the compiler's own waits more conservative.
-__device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(gbase), "s"(lds_addr)
-      : "memory", "m0");
-}
-
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)p;
 }

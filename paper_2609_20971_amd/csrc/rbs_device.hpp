@@ -70,6 +70,25 @@ __device__ __forceinline__ float wave_min(float x) { return wave_extreme<false>(
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// One 16-byte-per-lane global -> LDS copy: lane l's 16 bytes from gbase + voff
+// land at LDS byte lds_addr + 16 l.  Issued from inline assembly so that the
+// compiler's wait-count pass does not treat every later LDS read as dependent on
+// it (it would wait for all outstanding copies); the kernels wait for the copies
+// they need with explicit vmcnt counts instead.  Later-issued vector loads only
+// make the compiler's own waits more conservative.  s_nop: a copy needs one wait
+// state after the scalar write of m0, which the compiler's hazard pass does not
+// insert inside inline assembly; without it the copy may land at the previous
+// copy's LDS address.
+__device__ __forceinline__ void lds_dma16(const void* gbase, uint32_t voff, uint32_t lds_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(voff), "s"(gbase), "s"(lds_addr)
+      : "memory", "m0");
+}
+
 // 32x32x16 MFMA wrappers: D = A(32x16) B(16x32) + C.
 // Lane l supplies A[m = l%32][k = 8(l/32) .. +7] and B[k = 8(l/32) .. +7][n = l%32];
 // D[m][n] lives in lane n + 32((m/4)%2), element (m/8)*4 + m%4.

@@ -107,18 +107,6 @@ struct SelectLds {
 // 16-byte reads of one chunk of 32 rows).
 __device__ __forceinline__ int tile_chunk(int r, int c) { return c ^ (r & 15); }
 
-// One 16-byte-per-lane global -> LDS copy (lane l lands at lds_addr + 16 l).
-// From inline assembly, so that no LDS read waits for it by itself: the tile
-// loop waits with vmcnt(0) before the barrier that publishes a tile.
-__device__ __forceinline__ void tile_dma16(const void* gbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(gbase), "s"(lds_addr)
-      : "memory", "m0");
-}
-
 // LDS written by other lanes of this wave is read after this point (a wave's
 // LDS operations execute in order; the compiler must keep them so).
 __device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
@@ -178,8 +166,8 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
       const int r = kRows * wave + 4 * j + (lane >> 4);
       const uint32_t voff = (uint32_t)min(tile * kTile + r, M - 1) * (kHeadDim * 2) + 16 * tile_chunk(r, lane & 15);
       const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + (tile & 1) * kTileBytes + (kRows * wave + 4 * j) * 256);
-      tile_dma16(cg, voff, dst);
-      if constexpr (MODE == kSelectBox) tile_dma16(hg, voff, dst + 2 * kTileBytes);
+      lds_dma16(cg, voff, dst);
+      if constexpr (MODE == kSelectBox) lds_dma16(hg, voff, dst + 2 * kTileBytes);
     }
   };
   issue_tile(0);

@@ -37,18 +37,6 @@ __device__ __forceinline__ int vswz(int r, int c) { return c ^ ((r & 3) << 2); }
 // vmcnt(n) with expcnt/lgkmcnt left unconstrained (gfx9 encoding).
 #define RBS_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt((((n) & 15) | (((n) >> 4) << 14)) | 0x0F70)
 
-// Workgroup id -> logical work item, so that groups of 8 consecutive items
-// (the query heads of one KV group, same query block) run on the same XCD
-// (workgroups are dealt to the 8 XCDs round-robin by id) and share its L2.
-// Items are ordered KV-group-major, so all XCDs work on one KV head's K/V
-// (64 MiB at 128K) at a time and the Infinity Cache holds it.
-__device__ __forceinline__ int xcd_remap(int id, int total) {
-  const int full = total & ~63;
-  if (id >= full) return id;
-  const int x = id & 7, s = id >> 3;
-  return ((s >> 3) << 6) + (x << 3) + (s & 7);
-}
-
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)p;
 }
@@ -129,7 +117,7 @@ struct AttnCore {
   int64_t kv_head, kv_tok;  // the same for K and V
   int N, M, group;
   int ld;  // tokens between consecutive heads of lse (N, or the batch's total)
-  bool row_major;  // work order (work_of)
+  int order;  // WorkOrder
   float scale_log2;
   uint16_t* O;
   float* lse;
@@ -472,24 +460,6 @@ __device__ __forceinline__ void attend_block(const AttnCore& c, int h, int i, in
 }
 
 
-// Work slot id (of total = M hq) -> (query head, query block), late (long)
-// rows first, a group's query heads adjacent (and, through xcd_remap, on one
-// XCD).  Two orders: KV-group-major (all rows of one KV group, then the next),
-// or row-major (one query block of every head, then the block before it).
-__device__ __forceinline__ void work_of(int id, int total, int M, int hq, int group, bool row_major, int& h, int& i) {
-  const int work = xcd_remap(id, total);
-  if (row_major) {
-    i = M - 1 - work / hq;
-    h = work % hq;
-    return;
-  }
-  const int per_group = M * group;
-  const int g = work / per_group;
-  const int rem = work - g * per_group;
-  i = M - 1 - rem / group;
-  h = g * group + rem % group;
-}
-
 // Work queues of the persistent launches.  The hardware sends workgroup j to
 // XCD j % 8, and a one-workgroup-per-slot launch runs slot s on XCD s % 8.  A
 // persistent launch keeps that placement: workgroup j serves queue j % 8,
@@ -619,22 +589,6 @@ hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, PerIt
   return hipGetLastError();
 }
 
-// Whether a launch over n_kv_heads heads of n_tokens K and V rows (row_bytes for
-// the two together) takes its rows in row-major order.  That order starts the
-// longest rows of every head first, where the group-major order starts the
-// last group's longest rows last and ends on them alone, and it gives each XCD
-// one KV head (with up to 8) instead of all XCDs the same one; but it keeps all
-// KV heads in use at once.  The line is where they still fit the 256 MiB
-// Infinity Cache (half of it at B = 64, whose tiles are used for half as many
-// queries).  Attention, group-major against row-major: 3001 dense tokens, 32 / 4
-// heads 128 / 102 us, 8192 565 / 518, 16384 1966 / 1928, 16384 with 8 / 8 heads
-// 640 / 555, 64K with 64 / 8 heads 8.47 / 8.39 ms; past the line 128K with 64 / 8
-// heads 18.6 / 18.8 ms, 256K with 32 / 4 heads 23.3 / 23.6, 128K at B = 64 15.3 /
-// 15.45 ms.
-inline bool row_major_work(int n_tokens, int n_kv_heads, int row_bytes, int block_size) {
-  return (int64_t)n_tokens * n_kv_heads * row_bytes <= (block_size >= 128 ? 256 : 128) * (int64_t(1) << 20);
-}
-
 inline AttnCore make_attn_core(const AttnArgs& a) {
   AttnCore c;
   c.Q = a.Q;
@@ -648,7 +602,7 @@ inline AttnCore make_attn_core(const AttnArgs& a) {
   c.M = a.n_blocks;
   c.group = a.n_q_heads / a.n_kv_heads;
   c.ld = a.n_tokens;
-  c.row_major = row_major_work(a.n_tokens, a.n_kv_heads, 512, a.block_size);
+  c.order = work_order(a.n_tokens, a.n_q_heads, a.n_kv_heads, 512, a.block_size, a.n_blocks);
   c.scale_log2 = a.scale * kLog2e;
   c.O = a.O;
   c.lse = a.lse;

@@ -16,7 +16,7 @@ __device__ __forceinline__ void attend_slot(const AttnCore& c, const int32_t* __
                                             const int32_t* __restrict__ indices, int64_t capacity, int slot,
                                             int total, unsigned char* k_lds, unsigned char* v_lds, LastBlock last_block) {
   int h, i;
-  work_of(slot, total, c.M, total / c.M, c.group, c.row_major, h, i);
+  work_of(slot, total, c.M, total / c.M, c.group, c.order, h, i);
   const int count = min(max(counts[(size_t)h * c.M + i], 0), i + 1);
   const int32_t* list = indices + (int64_t)h * capacity + (int64_t)i * (i + 1) / 2;
   attend_block<BS>(c, h, i, count, [&](int n) __attribute__((always_inline)) { return list[n]; }, k_lds, v_lds,
@@ -58,7 +58,7 @@ __device__ __forceinline__ void attend_slot_varlen(AttnCore c, const int32_t* __
   const int hq = total / t.blk[t.n];  // query heads
   const int work = xcd_remap(slot, total);
   int sq, i, h;
-  if (c.row_major) {
+  if (c.order != kByGroup) {
     row_at(rows, work / hq, &sq, &i);
     h = work % hq;
   } else {
@@ -217,7 +217,9 @@ hipError_t launch_attention_varlen(const AttnArgs& a, const SeqTable& t, hipStre
   // sequences of 150 to 4000 tokens 165 / 136 us, 40 of 500 tokens 209 / 174; 16
   // of 1 to 7001 (25 K tokens) 951 / 952 us and at B = 64 687 / 704; three of 30 K
   // to 64 K 27.8 / 28.1 ms.
-  c.row_major = c.row_major && (int64_t)a.n_tokens * a.n_q_heads <= 3 << 18;
+  const bool by_row = row_major_work(a.n_tokens, a.n_kv_heads, 512, a.block_size) &&
+                      (int64_t)a.n_tokens * a.n_q_heads <= 3 << 18;
+  c.order = by_row ? kByRow : kByGroup;
   switch (a.block_size) {
     case 64: return launch_attention_varlen_bs<64>(c, a, t, s);
     case 128: return launch_attention_varlen_bs<128>(c, a, t, s);

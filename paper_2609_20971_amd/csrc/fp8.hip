@@ -299,7 +299,7 @@ struct AttnF8Args {
   const uint8_t* V8t;
   const float* amax;  // [H_q + 2 H_kv]: Q heads, K heads, V heads
   int N, M, Hq, Hkv;
-  bool row_major;     // work order (work_of)
+  int order;          // WorkOrder
   float scale_log2;   // softmax scale * log2(e)
   int64_t capacity;   // list slots per query head
   uint16_t* O;
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   __shared__ __align__(1024) unsigned char k_lds[2 * BS * 128];
   __shared__ __align__(1024) unsigned char v_lds[2 * kHeadDim * BS];
   int h, i;
-  work_of(blockIdx.x, gridDim.x, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
+  work_of(blockIdx.x, gridDim.x, c.M, c.Hq, c.Hq / c.Hkv, c.order, h, i);
   attend_block_fp8<BS>(c, counts, indices, h, i, k_lds, v_lds, [] {});
 }
 
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   QueueTicket ticket(queue);
   for (int slot = blockIdx.x; slot >= 0; slot = next_slot(ticket, total, &lds_slot)) {
     int h, i;
-    work_of(slot, total, c.M, c.Hq, c.Hq / c.Hkv, c.row_major, h, i);
+    work_of(slot, total, c.M, c.Hq, c.Hq / c.Hkv, c.order, h, i);
     attend_block_fp8<BS>(c, counts, indices, h, i, k_lds, v_lds, [&]() __attribute__((always_inline)) { ticket.take(); });
     __syncthreads();  // tiles and lds_slot free for the next item
   }
@@ -588,7 +588,7 @@ hipError_t launch_attention_fp8(const uint8_t* Q8, const uint8_t* K8, const uint
   a.M = n_blocks;
   a.Hq = n_q_heads;
   a.Hkv = n_kv_heads;
-  a.row_major = row_major_work(n_tokens, n_kv_heads, 256, block_size);
+  a.order = work_order(n_tokens, n_q_heads, n_kv_heads, 256, block_size, n_blocks);
   a.scale_log2 = scale * kLog2e;
   a.capacity = capacity;
   a.O = O;

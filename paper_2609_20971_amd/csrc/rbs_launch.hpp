@@ -156,6 +156,93 @@ __host__ __device__ inline void row_at(const RowOrder& o, int r, int* seq, int* 
   *i = o.blocks[lo - 1] - 1 - off / lo;
 }
 
+// Workgroup id -> logical work item, so that groups of 8 consecutive items (of a
+// group of 8: the query heads of one KV head, same query block) run on the same
+// XCD (workgroups are dealt to the 8 XCDs round-robin by id) and share its L2.
+__host__ __device__ inline int xcd_remap(int id, int total) {
+  const int full = total & ~63;
+  if (id >= full) return id;
+  const int x = id & 7, s = id >> 3;
+  return ((s >> 3) << 6) + (x << 3) + (s & 7);
+}
+
+// The order of a launch's work slots (query head, query block), late (long)
+// rows first in each.
+enum WorkOrder {
+  kByGroup = 0,  // all rows of one KV head's group, then the next group's: every XCD works on the same KV head
+  kByRow = 1,    // one query block of every head, then the block before it; 8 consecutive heads to an XCD
+  kByXcdRow = 2, // the same, each XCD on KV heads of its own
+};
+
+// Whether each XCD can have KV heads of its own: one head that 8 / n_kv XCDs
+// share, or n_kv / 8 heads.
+__host__ __device__ inline bool kv_heads_tile_xcds(int n_kv) { return n_kv <= 8 ? 8 % n_kv == 0 : n_kv % 8 == 0; }
+
+// Work slot id (of total = M hq) -> (query head h, query block i).
+__host__ __device__ inline void work_of(int id, int total, int M, int hq, int group, int order, int& h, int& i) {
+  if (order == kByXcdRow) {
+    // XCD id % 8 takes the rows of its own KV heads in order; the 8 / n_kv XCDs
+    // of one head every 8 / n_kv-th row each, up to the last full set of rows.
+    const int n_kv = hq / group;
+    const int sharing = n_kv < 8 ? 8 / n_kv : 1, own = n_kv < 8 ? 1 : n_kv / 8, heads = 8 / sharing;
+    const int rows = M - M % sharing;
+    if (id < rows * hq) {
+      const int x = id & 7, unit = (id >> 3) / group;  // unit: one row of one KV head
+      i = M - 1 - (unit / own * sharing + x / heads);
+      h = (x % heads + 8 * (unit % own)) * group + (id >> 3) % group;
+      return;
+    }
+  }
+  const int work = order == kByXcdRow ? id : xcd_remap(id, total);
+  if (order != kByGroup) {
+    i = M - 1 - work / hq;
+    h = work % hq;
+    return;
+  }
+  const int per_group = M * group;
+  const int g = work / per_group;
+  const int rem = work - g * per_group;
+  i = M - 1 - rem / group;
+  h = g * group + rem % group;
+}
+
+// Whether a launch over n_kv_heads heads of n_tokens K and V rows (row_bytes for
+// the two together) goes by rows.  That starts the longest rows of every head
+// first, where the order by groups starts the last group's longest rows last and
+// ends on them alone; but it keeps all KV heads in use at once.  The line is
+// where they still fit the 256 MiB Infinity Cache (half of it at B = 64, whose
+// tiles are used for half as many queries).  Attention, by group against by row:
+// 3001 dense tokens, 32 / 4 heads 128 / 102 us, 8192 565 / 518, 16384 1966 / 1928,
+// 16384 with 8 / 8 heads 640 / 555, 64K with 64 / 8 heads 8.47 / 8.39 ms; past the
+// line 128K with 64 / 8 heads 18.6 / 18.8 ms, 256K with 32 / 4 heads 23.3 / 23.6,
+// 128K at B = 64 15.3 / 15.45 ms.
+inline bool row_major_work(int n_tokens, int n_kv_heads, int row_bytes, int block_size) {
+  return (int64_t)n_tokens * n_kv_heads * row_bytes <= (block_size >= 128 ? 256 : 128) * (int64_t(1) << 20);
+}
+
+// The order of a launch over one sequence.  Eight consecutive heads per XCD are
+// one KV head for groups of 8 (both orders by rows are then the same); for other
+// groups every XCD reads up to all KV heads, whose K and V its 4 MB L2 does not
+// hold once many rows are in flight.  A KV head per XCD costs balance instead
+// (heads differ in density), so it takes launches of many items: sparse lists,
+// by row / by XCD's rows: 28 / 4 heads, B = 64, 16384 tokens (7168 items) 1374 /
+// 976 us (by group 1060), 40 / 8 8100 tokens (5080) 700 / 513 (580), 12 / 2 40000
+// tokens (7500) 1084 / 898 (920), 40 / 8, B = 128, 16384 (5120) 1181 / 1129
+// (1175); the other way at 16384 tokens, 8 / 8 heads, B = 64 (2048 items) 325 /
+// 390, B = 128 at 40000 tokens (2504) 584 / 616, and at B = 256 at every size (643
+// / 722 with 1256 items).  FP8 tiles are half the size: B = 64, 28 / 4, 8100
+// tokens (3556) 239 / 257, 16 / 16 16384 (4096) 326 / 344, 8 / 8 40000 (5000) 512
+// / 454.  KV heads that do not tile the XCDs, by row / by group: B = 64, 20 / 5,
+// 8100 tokens (2540) 264 / 324, 16384 (5120) 910 / 765; FP8 16384 423 / 467,
+// 40000 (12500) 1329 / 1152.
+inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row_bytes, int block_size, int n_blocks) {
+  if (!row_major_work(n_tokens, n_kv_heads, row_bytes, block_size)) return kByGroup;
+  const bool tiles = kv_heads_tile_xcds(n_kv_heads);
+  const int few = row_bytes > 256 ? 3072 : tiles ? 4096 : 8192;
+  if (block_size > 128 || n_blocks * n_q_heads <= few) return kByRow;
+  return tiles ? kByXcdRow : kByGroup;
+}
+
 inline SeqTable single_sequence(int n_tokens, int n_blocks) {
   SeqTable t{};
   t.n = 1;

@@ -1,0 +1,82 @@
+"""The attention launches' work order on the host (CPU only): every (query head,
+query block) once, longest rows first, and each XCD on few KV heads."""
+
+from __future__ import annotations
+
+import ctypes
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2609_20971_amd import build
+
+SOURCE = r"""
+#include "rbs_launch.hpp"
+using namespace rbs;
+extern "C" int choose(int n, int hq, int hkv, int row_bytes, int b, int M) {
+  return work_order(n, hq, hkv, row_bytes, b, M);
+}
+// Query head and query block of every work slot of one sequence.
+extern "C" void items(int M, int hq, int hkv, int order, int* h, int* i) {
+  for (int s = 0; s < M * hq; ++s) work_of(s, M * hq, M, hq, hq / hkv, order, h[s], i[s]);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("order")
+    (d / "order.hip").write_text(SOURCE)
+    subprocess.run([build.HIPCC, *build.FLAGS, "--cuda-host-only", "-I", build.CSRC, "-shared", str(d / "order.hip"),
+                    "-o", str(d / "order.so")], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    return ctypes.CDLL(str(d / "order.so"))
+
+
+BY_GROUP, BY_ROW, BY_XCD_ROW = 0, 1, 2
+
+
+def _items(lib, M, hq, hkv, order):
+    h, i = np.full(M * hq, -1, np.int32), np.full(M * hq, -1, np.int32)
+    lib.items(M, hq, hkv, order, h.ctypes.data_as(ctypes.c_void_p), i.ctypes.data_as(ctypes.c_void_p))
+    return h, i
+
+
+def _tiles(hkv):
+    return 8 % hkv == 0 or hkv % 8 == 0
+
+
+HEADS = [(1, 1), (2, 1), (7, 1), (8, 1), (12, 2), (16, 2), (28, 4), (32, 4), (8, 8), (40, 8), (64, 8), (16, 16),
+         (32, 16), (3, 3), (6, 3), (20, 5), (36, 12)]
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("M", [1, 2, 5, 8, 31, 64, 513])
+def test_every_item_once_and_longest_rows_first(lib, hq, hkv, M):
+    for order in (BY_GROUP, BY_ROW) + ((BY_XCD_ROW,) if _tiles(hkv) else ()):
+        h, i = _items(lib, M, hq, hkv, order)
+        assert np.array_equal(np.unique(h.astype(np.int64) * M + i), np.arange(M * hq))
+        if order != BY_GROUP:
+            for x in range(8):  # in-order dispatch and each queue start an XCD's longest rows first
+                assert (np.diff(i[x::8]) <= 0).all()
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+@pytest.mark.parametrize("B", [64, 128])
+@pytest.mark.parametrize("row_bytes", [512, 256])
+def test_a_launch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv, B, row_bytes):
+    """Past 3072 (FP8: 4096, or 8192) items an XCD (slots x, x + 8, ...) works on one KV
+    head at a time, or on n_kv / 8 of its own, whatever the head counts."""
+    for n in (8100, 16384, 40000, 65536, 131072):
+        M = -(-n // B)
+        order = lib.choose(n, hq, hkv, row_bytes, B, M)
+        assert order != BY_XCD_ROW or _tiles(hkv)
+        if M * hq <= (3072 if row_bytes > 256 else 4096 if _tiles(hkv) else 8192):
+            continue
+        h, i = _items(lib, M, hq, hkv, order)
+        for x in range(8):
+            mine = (h // (hq // hkv))[x::8][i[x::8] >= 8]  # (the last, shortest rows may be anyone's)
+            if order == BY_GROUP:  # one after another
+                assert (np.diff(mine) >= 0).all()
+            else:
+                assert len(np.unique(mine)) <= max(1, hkv // 8), (n, x, np.unique(mine))

@@ -211,15 +211,7 @@ static hipError_t launch_attention_varlen_bs(const AttnCore& c, const AttnArgs& 
 
 hipError_t launch_attention_varlen(const AttnArgs& a, const SeqTable& t, hipStream_t s) {
   AttnCore c = make_attn_core(a);
-  // Of a large batch the sequences one after another: their rows keep the
-  // balance by themselves, and each sequence's K and V are used while they are
-  // near.  Sequence-major against longest rows first, 32 / 4 heads, B = 128: 4
-  // sequences of 150 to 4000 tokens 165 / 136 us, 40 of 500 tokens 209 / 174; 16
-  // of 1 to 7001 (25 K tokens) 951 / 952 us and at B = 64 687 / 704; three of 30 K
-  // to 64 K 27.8 / 28.1 ms.
-  const bool by_row = row_major_work(a.n_tokens, a.n_kv_heads, 512, a.block_size) &&
-                      (int64_t)a.n_tokens * a.n_q_heads <= 3 << 18;
-  c.order = by_row ? kByRow : kByGroup;
+  c.order = batch_order(a.n_tokens, a.n_q_heads, a.n_kv_heads, a.block_size, a.n_blocks);
   switch (a.block_size) {
     case 64: return launch_attention_varlen_bs<64>(c, a, t, s);
     case 128: return launch_attention_varlen_bs<128>(c, a, t, s);

@@ -243,6 +243,23 @@ inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row
   return tiles ? kByXcdRow : kByGroup;
 }
 
+// The order of a launch over a batch: the longest rows of all sequences first
+// (kByRow), or the sequences one after another (kByGroup).  The rows of a large
+// batch keep the balance by themselves, and one sequence after another uses each
+// one's K and V while they are near.  By sequence against by row, 32 / 4 heads,
+// B = 128: 4 sequences of 150 to 4000 tokens 165 / 136 us, 40 of 500 tokens 209 /
+// 174; 16 of 1 to 7001 (30 K tokens) 951 / 952 us and at B = 64 687 / 704; three
+// of 30 K to 64 K 27.8 / 28.1 ms.  At B = 64 and groups other than 8 as for one
+// sequence (work_order): two sequences, 28 / 4 heads (27 K tokens) 742 / 886 us,
+// 40 / 8 (19 K) 802 / 1031, 20 / 5 (38 K) 1109 / 1518; B = 128 1859 / 1866, 1514 /
+// 1515, 2502 / 2480.
+inline WorkOrder batch_order(int n_tokens, int n_q_heads, int n_kv_heads, int block_size, int n_blocks) {
+  if (!row_major_work(n_tokens, n_kv_heads, 512, block_size)) return kByGroup;
+  if ((int64_t)n_tokens * n_q_heads > 3 << 18) return kByGroup;
+  const bool eighths = n_q_heads / n_kv_heads % 8 == 0;  // eight consecutive heads share a KV head
+  return block_size > 64 || eighths || n_blocks * n_q_heads <= 3072 ? kByRow : kByGroup;
+}
+
 inline SeqTable single_sequence(int n_tokens, int n_blocks) {
   SeqTable t{};
   t.n = 1;

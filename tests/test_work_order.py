@@ -17,6 +17,7 @@ using namespace rbs;
 extern "C" int choose(int n, int hq, int hkv, int row_bytes, int b, int M) {
   return work_order(n, hq, hkv, row_bytes, b, M);
 }
+extern "C" int choose_batch(int n, int hq, int hkv, int b, int blocks) { return batch_order(n, hq, hkv, b, blocks); }
 // Query head and query block of every work slot of one sequence.
 extern "C" void items(int M, int hq, int hkv, int order, int* h, int* i) {
   for (int s = 0; s < M * hq; ++s) work_of(s, M * hq, M, hq, hq / hkv, order, h[s], i[s]);
@@ -80,3 +81,15 @@ def test_a_launch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv, B, ro
                 assert (np.diff(mine) >= 0).all()
             else:
                 assert len(np.unique(mine)) <= max(1, hkv // 8), (n, x, np.unique(mine))
+
+
+@pytest.mark.parametrize("hq,hkv", HEADS)
+def test_a_batch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv):
+    """At B = 64 and past 3072 items a batch goes by rows only where eight
+    consecutive heads, an XCD's, share a KV head."""
+    for n in (2000, 8000, 19070, 27244, 60000):
+        order = lib.choose_batch(n, hq, hkv, 64, n // 64 + 2)
+        if (n // 64 + 2) * hq > 3072 and (hq // hkv) % 8:
+            assert order == BY_GROUP, n
+        elif n * hq <= 3 << 18 and n * hkv <= 1 << 18:
+            assert order == BY_ROW, n

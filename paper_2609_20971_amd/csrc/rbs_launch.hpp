@@ -260,6 +260,32 @@ inline WorkOrder batch_order(int n_tokens, int n_q_heads, int n_kv_heads, int bl
   return block_size > 64 || eighths || n_blocks * n_q_heads <= 3072 ? kByRow : kByGroup;
 }
 
+// Tokens that one wave of a selection launch scores: a row (query block) of B
+// tokens takes B / row_tokens waves.  rows: query heads x query blocks of the
+// launch; n_blocks: of its longest sequence.
+// Long rows (past kSharedRowBlocks blocks) are the launch's time by themselves
+// where there are few: 32 tokens a wave, so that a row's tiles are scored side by
+// side.  32 / 64 / 128 tokens a wave, B = 128, selection alone: 41200 tokens, 2
+// heads (644 rows) 19.0 / 21.6 / 28.0 us, 70000 (1094) 27.2 / 31.4 / 43.0, 100000
+// (1564) 44.8 / 43.6 / 54.5; 4 heads 41200 (1288) 25.9 / 24.9 / 33.2; box selector
+// 70000, 2 heads 60 / 64 / 84; B = 64 30000, 2 heads (938) 20.9 / 23.6, box 44 /
+// 52, 4 heads (1876) 23.4 / 25.2, 64000 tokens 65.5 / 56.8.
+// B = 128, more rows: shared by two waves a row holds 64 VGPRs of Q in each and
+// runs at three waves per SIMD instead of two, which covers short rows' latencies
+// better; long rows are bound by their tiles, where one wave per row reads each
+// staged operand half as often.  64 / 128 tokens a wave, 32 / 4 heads: 16K (128
+// blocks) 36.9 / 41.4 us, 32K 82 / 88, 45K (352) 146 / 141, 64K 255 / 241, 128K
+// 770 / 696; fewer rows: 8 heads 52000 (3256) 46.6 / 52.5, 6 heads 100000 (4692)
+// 91.9 / 90.0, 4 heads 128K (4096) 99.4 / 94.4.
+// B = 256: 64 against 128 32K 64 / 87 us, 128K 500 / 505, 256K 1575 / 1538.
+constexpr int kSharedRowBlocks = 320;
+constexpr int kFewRows = 1200, kSharedRows = 4000;
+inline int row_tokens(int block_size, int n_blocks, int rows) {
+  const bool long_rows = n_blocks > kSharedRowBlocks;
+  if (block_size <= 128 && long_rows && rows <= kFewRows) return 32;
+  return block_size == 128 && long_rows && rows > kSharedRows ? 128 : 64;
+}
+
 inline SeqTable single_sequence(int n_tokens, int n_blocks) {
   SeqTable t{};
   t.n = 1;

@@ -1,9 +1,9 @@
 // Stage 2: dual-branch block selection (Sec. 3.2; Algorithm 1, selection loop)
 // and the supporting selectors of the paper's selector comparison.
 //
-// A wave scores the key blocks of one row (query head h, query block i) for 64
-// or 128 of its tokens (RowSplit): a whole row where it can, otherwise two or
-// four waves share it.  The wave's Q rows are read from HBM once and held in
+// A wave scores the key blocks of one row (query head h, query block i) for 32,
+// 64 or 128 of its tokens (row_tokens): a whole row, or two or four waves share
+// it.  The wave's Q rows are read from HBM once and held in
 // registers as f16 (bf16 -> f16 is exact in the normal range).  Candidate key
 // blocks 0..i are scored in tiles of 32 centroids that the workgroup's waves --
 // rows of one KV head, next to each other in the work order -- stage through
@@ -47,7 +47,6 @@ constexpr int kTileBytes = kTile * kHeadDim * 2;
 // every term above fp32's normal minimum 2^-126.
 constexpr float kPlainBound = 112.0f;
 constexpr float kCandSlack = 1e-2f;  // log2 units: rounding allowance of the rescue-candidate test
-constexpr int kSharedRowBlocks = 320;  // B = 128: rows of up to this many blocks are shared by two waves
 constexpr int kCandRing = 128;       // pending rescue candidates of a wave: at most 31 + 64
 
 // Selection policies: the method's dual-branch selector and the three
@@ -91,7 +90,7 @@ struct RowSplit {
 
 // LDS layout (byte offsets): centroid tiles (and half-width tiles, box), two of
 // each | |q| of every wave's tokens | per wave, the ring of pending rescue
-// candidates (dual) | the groups' pairs of two tiles (a row of two waves) | L
+// candidates (dual) | the groups' pairs of two tiles (a shared row) | L
 // (block scores) of every row.
 template <int BS, int MODE, int T, int W>
 struct SelectLds {
@@ -217,7 +216,7 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
       nq_row = fmaxf(nq_row, stage[w].x);
       nq_min = fminf(nq_min, stage[w].y);
     }
-    // (Read by both waves before the tile loop's first barrier, written after it.)
+    // (Read by the row's waves before the tile loop's first barrier, written after it.)
   }
 
   // ---- Scores of one tile of 32 key blocks, centroid rows in op (lane: block
@@ -332,7 +331,7 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
   auto merge_own = [&](bool plain) __attribute__((always_inline)) {
     return merge(plain, [&](int k) { return gm[k]; }, [&](int k) { return gs[k]; });
   };
-  // A row of two waves: the wave's pairs to the stage, and the merge from it
+  // A shared row: the wave's pairs to the stage, and the merge from it
   // (after a barrier).
   auto put_stage = [&](int buf) __attribute__((always_inline)) {
     if (half == 0) {
@@ -562,7 +561,7 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
 // Waves per SIMD that the register budget is set for: the wave's Q takes one
 // VGPR per token.
 template <int T>
-constexpr int kWavesPerEu = T == 64 ? 3 : 2;
+constexpr int kWavesPerEu = T == 32 ? 4 : T == 64 ? 3 : 2;
 
 // Workgroup j takes chunk j / n_kv of KV head j % n_kv: late (long) rows first
 // over all heads, and with 1, 2, 4 or 8 KV heads each XCD (workgroup j runs on
@@ -657,36 +656,34 @@ static hipError_t launch_select_mode(const SelectCore& c, int mode, hipStream_t 
   }
 }
 
-// f(integral_constant<int, T>, integral_constant<int, W>) with the split of rows
-// of up to M blocks.
+// f(integral_constant<int, T>, integral_constant<int, W>) with the split of
+// `rows` rows of up to M blocks.
 template <int BS, typename F>
-static hipError_t with_split(int M, F f) {
+static hipError_t with_split(int M, int rows, F f) {
+  const int tokens = row_tokens(BS, M, rows);
   constexpr std::integral_constant<int, 64> t64{};
-  constexpr std::integral_constant<int, 128> t128{};
   constexpr std::integral_constant<int, 2> w2{};
   constexpr std::integral_constant<int, 4> w4{};
-  if constexpr (BS == 64) {
-    // Four rows per workgroup (128K: 1253 us, two rows 1500, eight 1490), until
-    // their score rows leave a compute unit's 160 KB of LDS to one workgroup
-    // (256K: 7670 us, two rows 6530).
-    if (2 * SelectLds<BS, kSelectDual, 64, 4>::bytes(M) > 160 * 1024) return f(t64, w2);
+  if constexpr (BS == 256) {
     return f(t64, w4);
-  } else if constexpr (BS == 128) {
-    // A row shared by two waves holds 64 VGPRs of Q each and runs at three waves
-    // per SIMD instead of two, which covers short rows' latencies better; long
-    // rows are bound by their tiles, where one wave per row reads each staged
-    // operand half as often.  Shared / whole, 32 / 4 heads: 16K (128 blocks) 36.9
-    // / 41.4 us, 32K 82 / 88, 45K (352) 146 / 141, 64K 255 / 241, 128K 770 / 696.
-    if (M <= kSharedRowBlocks) return f(t64, w2);
-    return f(t128, w4);
   } else {
-    return f(t64, w4);  // against two waves of 128 tokens: 32K 64 / 87 us, 128K 500 / 505, 256K 1575 / 1538
+    if (tokens == 32) return f(std::integral_constant<int, 32>{}, std::integral_constant<int, BS / 32>{});
+    if constexpr (BS == 128) {
+      if (tokens == 64) return f(t64, w2);
+      return f(std::integral_constant<int, 128>{}, w4);
+    } else {
+      // Four rows per workgroup (128K: 1253 us, two rows 1500, eight 1490), until
+      // their score rows leave a compute unit's 160 KB of LDS to one workgroup
+      // (256K: 7670 us, two rows 6530).
+      if (2 * SelectLds<BS, kSelectDual, 64, 4>::bytes(M) > 160 * 1024) return f(t64, w2);
+      return f(t64, w4);
+    }
   }
 }
 
 template <int BS>
 static hipError_t launch_select_bs(const SelectCore& c, int mode, hipStream_t s) {
-  return with_split<BS>(c.M, [&](auto t, auto w) {
+  return with_split<BS>(c.M, c.M * c.group * c.n_kv, [&](auto t, auto w) {
     return launch_select_mode<BS, decltype(t)::value, decltype(w)::value>(c, mode, s);
   });
 }
@@ -707,7 +704,7 @@ template <int BS>
 static hipError_t launch_select_varlen_bs(const SelectCore& c, const SeqTable& t, hipStream_t s) {
   int m_max = 0;
   for (int q = 0; q < t.n; ++q) m_max = t.blk[q + 1] - t.blk[q] > m_max ? t.blk[q + 1] - t.blk[q] : m_max;
-  return with_split<BS>(m_max, [&](auto tok, auto w) {
+  return with_split<BS>(m_max, t.blk[t.n] * c.group * c.n_kv, [&](auto tok, auto w) {
     return launch_select_varlen_w<BS, decltype(tok)::value, decltype(w)::value>(c, t, m_max, s);
   });
 }

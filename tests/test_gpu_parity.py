@@ -117,9 +117,12 @@ def test_multiblock_rows(variant):
 
 @pytest.mark.parametrize("n,heads,block_size", [
     (128 * 320 - 3, (3, 1), 128),   # rows shared by two waves (up to 320 blocks), 3 heads: rows of different blocks
-    (128 * 321, (3, 1), 128),       # one wave per row, four rows a workgroup, the last workgroup partial
-    (128 * 321 + 1, (5, 5), 128),   # no GQA: every row of a workgroup another query block; a last block of one token
+    (128 * 321, (3, 1), 128),       # 963 long rows: 32 tokens a wave
+    (128 * 321 + 1, (5, 5), 128),   # 1610 long rows, no GQA: shared by two waves; a last block of one token
+    (128 * 321, (15, 5), 128),      # 4815: one wave per row, four rows a workgroup, the last workgroup partial
+    (128 * 321 + 1, (13, 13), 128), # the same without GQA: every row of a workgroup another query block
     (64 * 65 + 33, (7, 1), 64),     # 66 blocks, a last block of 33 tokens (a full group of 32 and one token)
+    (64 * 330 + 1, (3, 1), 64),     # 993 long rows: 32 tokens a wave, the last block in the first of two waves
     (256 * 33 + 64, (2, 1), 256),   # rows shared by four waves, two of them without a token in the last block
     (64 * 3900, (1, 1), 64),        # score rows too long for four rows a workgroup
 ])

@@ -1,5 +1,6 @@
-"""The attention launches' work order on the host (CPU only): every (query head,
-query block) once, longest rows first, and each XCD on few KV heads."""
+"""How launches are split and ordered, on the host (CPU only): every (query head,
+query block) of an attention launch once, longest rows first, and each XCD on few
+KV heads; a selection launch of few long rows over enough waves."""
 
 from __future__ import annotations
 
@@ -18,6 +19,7 @@ extern "C" int choose(int n, int hq, int hkv, int row_bytes, int b, int M) {
   return work_order(n, hq, hkv, row_bytes, b, M);
 }
 extern "C" int choose_batch(int n, int hq, int hkv, int b, int blocks) { return batch_order(n, hq, hkv, b, blocks); }
+extern "C" int tokens_a_wave(int b, int blocks, int rows) { return row_tokens(b, blocks, rows); }
 // Query head and query block of every work slot of one sequence.
 extern "C" void items(int M, int hq, int hkv, int order, int* h, int* i) {
   for (int s = 0; s < M * hq; ++s) work_of(s, M * hq, M, hq, hq / hkv, order, h[s], i[s]);
@@ -93,3 +95,17 @@ def test_a_batch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv):
             assert order == BY_GROUP, n
         elif n * hq <= 3 << 18 and n * hkv <= 1 << 18:
             assert order == BY_ROW, n
+
+
+@pytest.mark.parametrize("B", [64, 128, 256])
+def test_few_long_rows_are_split_over_more_waves(lib, B):
+    """A selection launch never leaves more than half of the 1024 SIMDs without a
+    wave while a wave still scores more than 32 tokens of a long row (B = 256:
+    64), and takes two waves a row of B = 128 up to 4000 rows."""
+    for blocks in (1, 320, 321, 547, 1024, 2048, 4096):
+        for rows in (blocks, 2 * blocks, 4 * blocks, 8 * blocks, 32 * blocks):
+            t = lib.tokens_a_wave(B, blocks, rows)
+            assert t in (32, 64, 128) and t <= B and (t > 32 or B < 256)
+            if blocks > 320:
+                assert t <= (32 if B < 256 else 64) or rows * (B // t) > 512
+                assert t <= 64 or rows > 4000

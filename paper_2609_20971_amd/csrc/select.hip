@@ -513,15 +513,45 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
   uint32_t kth_key = 0u;
   if constexpr (MODE == kSelectBox) {
     const int k = max(1, min(n_cand, (int)ceil((double)c.budget * (double)n_cand - 1e-12)));
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t cand_key = kth_key | (1u << bit);
-      int total = 0;
-      for (int base = 0; base < n_cand; base += kWave) {
-        const int b = base + lane;
-        total += __popcll(__ballot(b < n_cand && okey(L[min(b, n_cand - 1)]) >= cand_key));
+    auto search = [&](auto count_from) __attribute__((always_inline)) {
+      for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t cand_key = kth_key | (1u << bit);
+        const int total = count_from(cand_key);
+        if (total >= k) kth_key = cand_key;
+        if (total == k) break;
       }
-      if (total >= k) kth_key = cand_key;
-      if (total == k) break;
+    };
+    // Four scores a lane at a time: one at a time, each of a row's 32 x n_cand / 64
+    // steps waits for its LDS read (131072 tokens, 1 head, B = 128: 94 us, now 70).
+    // (No searched key is 0: a slot past the row is never counted.)
+    uint32_t key[4];
+    auto load4 = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int b = base + j * kWave + lane;
+        key[j] = b < n_cand ? okey(L[b]) : 0u;
+      }
+    };
+    auto count4 = [&](uint32_t cand_key) __attribute__((always_inline)) {
+      int total = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) total += __popcll(__ballot(key[j] >= cand_key));
+      return total;
+    };
+    if (n_cand <= 4 * kWave) {
+      load4(0);
+      search(count4);
+    } else {
+      search([&](uint32_t cand_key) __attribute__((always_inline)) {
+        int total = 0, base = 0;
+        for (; base + 4 * kWave <= n_cand; base += 4 * kWave) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) key[j] = okey(L[base + j * kWave + lane]);
+          total += count4(cand_key);
+        }
+        load4(base);
+        return total + count4(cand_key);
+      });
     }
   }
 

@@ -139,7 +139,8 @@ def test_selection_row_splits(n, heads, block_size):
     st = rbs.rbs_block_stats(shape, Kd)
     M = w.n_blocks
     rows = H.sample_rows(heads[0], M, 24, seed=3, include=[(0, M - 1), (heads[0] - 1, M - 1), (0, M - 2), (0, 0),
-                                                           (heads[0] - 1, min(M - 1, 32)), (0, min(M - 1, 64))])
+                                                           (heads[0] - 1, min(M - 1, 32)), (0, min(M - 1, 64)),
+                                                           (0, min(M - 1, 255)), (0, min(M - 1, 256))])
     C, R = oracle.block_stats(f64_from_bf16_bits(inp["k"]), block_size)
     beta, _ = oracle.rescue_coefficients(R)
     Qf = f64_from_bf16_bits(inp["q"])
@@ -155,7 +156,7 @@ def test_selection_row_splits(n, heads, block_size):
         H.check_lists(H.gpu_rows(counts, indices, every), M, w.n_sink, w.n_local, w.n_recent)
     del ref
     for variant, param in (("centroid", 0.9), ("full_l2", 0.9), ("box", 0.1)):
-        _variant_check(w, variant, param, rows=rows[:12], inputs=inp)
+        _variant_check(w, variant, param, rows=rows[:16], inputs=inp)
 
 
 @pytest.mark.parametrize("tau,forced", [

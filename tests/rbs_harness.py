@@ -107,8 +107,9 @@ def check_lists(lists, n_blocks, n_sink, n_local, n_recent):
         assert set(forced.tolist()) <= set(ids), f"row {(h, i)} misses forced blocks"
 
 
-def compare_masks(gpu_lists, oracle_rows):
-    """Return (n_rows, n_blocks_compared, near_flips); assert no other flip."""
+def compare_masks(gpu_lists, oracle_rows, bands=None):
+    """Return (n_rows, n_blocks_compared, near_flips); assert no other flip.
+    bands: near-threshold band of each row where it is not MARGIN_BAND."""
     near = 0
     compared = 0
     for key, ids in gpu_lists.items():
@@ -117,6 +118,7 @@ def compare_masks(gpu_lists, oracle_rows):
         g[ids] = True
         compared += g.shape[0]
         diff = np.nonzero(g != ref["final"])[0]
+        band = MARGIN_BAND if bands is None else bands[key]
         for b in diff:
             assert not ref["forced"][b], f"forced block {b} differs in row {key}"
             if "margin" in ref:  # single-branch supporting selector
@@ -126,11 +128,11 @@ def compare_masks(gpu_lists, oracle_rows):
             if ref["final"][b]:
                 # The oracle keeps it, the GPU drops it: every branch that keeps
                 # it must do so from inside the band.
-                ok = all(m <= MARGIN_BAND for m in margins if m >= 0)
+                ok = all(m <= band for m in margins if m >= 0)
             else:
                 # The GPU keeps it, the oracle drops it: some branch must miss
                 # its threshold by no more than the band.
-                ok = any(-MARGIN_BAND <= m < 0 for m in margins)
+                ok = any(-band <= m < 0 for m in margins)
             assert ok, (f"row {key} block {b}: gpu={bool(g[b])} oracle={bool(ref['final'][b])} "
                         f"margins {', '.join(f'{m:.3g}' for m in margins)}")
             near += 1

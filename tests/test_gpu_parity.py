@@ -3,6 +3,7 @@ same seeded inputs.  Tolerances live in tests/rbs_harness.py."""
 
 from __future__ import annotations
 
+import math
 import sys
 
 import numpy as np
@@ -156,7 +157,7 @@ def test_selection_row_splits(n, heads, block_size):
         H.check_lists(H.gpu_rows(counts, indices, every), M, w.n_sink, w.n_local, w.n_recent)
     del ref
     for variant, param in (("centroid", 0.9), ("full_l2", 0.9), ("box", 0.1)):
-        _variant_check(w, variant, param, rows=rows[:16], inputs=inp)
+        _variant_check(w, variant, param, rows=rows[:16], inputs=inp, box_bands=variant == "box")
 
 
 @pytest.mark.parametrize("tau,forced", [
@@ -450,7 +451,23 @@ def test_fused_select_attend_128k_matches_two_calls():
 
 # ------------------------------------------------ supporting selectors (Table selector_ablation)
 
-def _variant_check(w: Workload, variant: str, param: float, rows=None, inputs=None):
+def _box_bands(Qf, Vc, Hw, w: Workload, rows):
+    """How far from the budget's line a block of the box selector may be taken
+    otherwise, per row.  Centre and half-width are rounded to f16 (relative error
+    uniform in +-2^-11), so a token's logit q.v + |q|.h is off by a sum of
+    independent errors of standard deviation 2^-11 / sqrt(3) sqrt(q^2.(v^2 + h^2)) /
+    sqrt(d), and a block score, a log-sum-exp, by no more than its worst token.  Six
+    standard deviations of the difference of two scores; box logits of 75 give 0.01."""
+    bands = {}
+    for h, i in rows:
+        g = h * w.n_kv_heads // w.n_q_heads
+        q2 = Qf[h, i * w.block_size:(i + 1) * w.block_size] ** 2
+        var = (q2 @ (Vc[g, :i + 1] ** 2 + Hw[g, :i + 1] ** 2).T).max() / q2.shape[1]
+        bands[(h, i)] = max(H.MARGIN_BAND, 6 * math.sqrt(2 * var / 3) * 2.0 ** -11)
+    return bands
+
+
+def _variant_check(w: Workload, variant: str, param: float, rows=None, inputs=None, box_bands=False):
     """A supporting selector through the C ABI against the oracle's: box
     statistics to fp32 rounding, lists bit for bit outside the near-threshold
     band, the same structural invariants as the method's lists."""
@@ -483,7 +500,7 @@ def _variant_check(w: Workload, variant: str, param: float, rows=None, inputs=No
                                 w.n_recent, rows=rows)
     lists = H.gpu_rows(counts, indices, rows)
     H.check_lists(lists, M, w.n_sink, w.n_local, w.n_recent)
-    n_rows, compared, near = H.compare_masks(lists, ref)
+    n_rows, compared, near = H.compare_masks(lists, ref, _box_bands(Qf, Vc, Hw, w, rows) if box_bands else None)
     dens = sum(len(v) for v in lists.values()) / compared
     _say(f"[parity] selector {variant}({param}) {w.name} N={w.seq_len} B={w.block_size}: rows {n_rows} "
          f"blocks {compared} near-threshold flips {near}; density {dens:.4f}")

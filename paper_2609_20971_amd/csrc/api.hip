@@ -391,11 +391,15 @@ int rbs_select_attend(const rbs_shape* shape, const void* Q, const void* K, cons
   aa.O = static_cast<uint16_t*>(O);
   aa.lse = lse;
   aa.queue = static_cast<int*>(workspace);
+  aa.selected = true;
   rc = check_q_range(Q, st.q_head, st.q_tok, shape->n_q_heads, shape->n_tokens, stream);
   if (rc != RBS_OK) return rc;
   // The two stages' own kernels, one after the other: a kernel that did both
   // kept its selection at the attention's occupancy (2 workgroups per compute
-  // unit) and was slower at every block size.
+  // unit) and was slower nearly everywhere.  One kernel / two, whole calls: 64K
+  // tokens, 64 / 8 heads, B = 128 26.5 / 25.5 ms; B = 64, 32 / 4 heads 8000 tokens
+  // 242 / 239 us, 8 / 1 20000 246 / 244; the other way 59084 tokens with one head
+  // (selection and attention both a few rows' latency) 174 / 186.
   hipError_t e = rbs::launch_select(sa, static_cast<hipStream_t>(stream));
   if (e == hipSuccess) e = rbs::launch_attention(aa, static_cast<hipStream_t>(stream));
   return finish(e, stream);

@@ -560,18 +560,20 @@ hipError_t resident_grid(int threads, int* grid) {
 }
 
 // One launch of total work slots by workgroups of `threads`: persistent
-// through the queues when the caller gave them and there are more than three
-// times as many slots as the device holds at once, otherwise one workgroup per
-// slot.  Few slots leave little to hand out, and the counter reset's launch and
-// the tickets are saved; with many, in-order dispatch holds slots back where the
-// rows' lengths differ.  Queues against per slot, 32 heads: 700 dense tokens (0.4
+// through the queues when the caller gave them and there are more slots than
+// line(resident), resident being what the device holds at once; otherwise one
+// workgroup per slot.  Few slots leave little to hand out, and the counter reset's
+// launch and the tickets are saved; with many, in-order dispatch holds slots back
+// where the rows' lengths differ.  The general line is three times the resident
+// workgroups.  Queues against per slot, 32 heads: 700 dense tokens (0.4
 // times the resident slots) 25.7 / 19.9 us, 3001 (1.5 times) 99 / 89, 6000 (3
 // times) 299 / 288 dense and 251 / 251 on sparse lists, 8100 (4 times) 518 / 507
 // dense and 397 / 438 sparse; B = 64 6000 343 / 325 and 300 / 283, 8100 590 / 566
-// and 442 / 476.
+// and 442 / 476.  (A persistent workgroup j runs slot j first, so the grid is
+// never larger than total.)
 // per_item(grid) and queued(grid) launch the two forms.
-template <auto QueueKernel, typename PerItem, typename Queued>
-hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, PerItem per_item, Queued queued) {
+template <auto QueueKernel, typename Line, typename PerItem, typename Queued>
+hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, Line line, PerItem per_item, Queued queued) {
   if (queue == nullptr) {
     per_item(total);
     return hipGetLastError();
@@ -579,7 +581,7 @@ hipError_t launch_slots(int threads, int total, int* queue, hipStream_t s, PerIt
   int resident = 0;
   hipError_t e = resident_grid<QueueKernel>(threads, &resident);
   if (e != hipSuccess) return e;
-  if (total <= 3 * resident) {
+  if (total <= resident || total <= line(resident)) {
     per_item(total);
     return hipGetLastError();
   }
@@ -602,7 +604,7 @@ inline AttnCore make_attn_core(const AttnArgs& a) {
   c.M = a.n_blocks;
   c.group = a.n_q_heads / a.n_kv_heads;
   c.ld = a.n_tokens;
-  c.order = work_order(a.n_tokens, a.n_q_heads, a.n_kv_heads, 512, a.block_size, a.n_blocks);
+  c.order = work_order(a.n_tokens, a.n_q_heads, a.n_kv_heads, 512, a.block_size, a.n_blocks, a.selected);
   c.scale_log2 = a.scale * kLog2e;
   c.O = a.O;
   c.lse = a.lse;

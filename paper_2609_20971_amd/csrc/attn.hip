@@ -165,6 +165,7 @@ static hipError_t launch_attention_bs(const AttnCore& c, const AttnArgs& a, hipS
   const int total = a.n_blocks * a.n_q_heads;
   return launch_slots<attn_queue_kernel<BS>>(
       BS * 2, total, a.queue, s,
+      [&](int resident) { return queue_line(a.n_tokens, a.n_q_heads, a.n_kv_heads, BS, a.n_blocks, resident, a.selected); },
       [&](int grid) {
         hipLaunchKernelGGL(attn_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, a.capacity);
       },
@@ -199,7 +200,7 @@ static hipError_t launch_attention_varlen_bs(const AttnCore& c, const AttnArgs& 
   const int total = t.blk[t.n] * a.n_q_heads;
   const RowOrder rows = rows_by_length(t);
   return launch_slots<attn_varlen_queue_kernel<BS>>(
-      BS * 2, total, a.queue, s,
+      BS * 2, total, a.queue, s, [](int resident) { return 3 * resident; },
       [&](int grid) {
         hipLaunchKernelGGL(attn_varlen_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, c, a.counts, a.indices, t, rows);
       },

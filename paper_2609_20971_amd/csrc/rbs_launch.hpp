@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 namespace rbs {
@@ -67,6 +68,7 @@ struct AttnArgs {
   uint16_t* O;
   float* lse;
   int* queue = nullptr;  // persistent launch's work queues (kQueueInts ints), or one workgroup per item
+  bool selected = false;  // the lists are this call's own selection (work_order, queue_line)
 };
 
 // Select-ready summary, each part 256-byte aligned: f16 centroids scaled by
@@ -235,12 +237,52 @@ inline bool row_major_work(int n_tokens, int n_kv_heads, int row_bytes, int bloc
 // / 454.  KV heads that do not tile the XCDs, by row / by group: B = 64, 20 / 5,
 // 8100 tokens (2540) 264 / 324, 16384 (5120) 910 / 765; FP8 16384 423 / 467,
 // 40000 (12500) 1329 / 1152.
-inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row_bytes, int block_size, int n_blocks) {
+//
+// B = 64 and a whole number of KV heads per XCD (own_head_rows): from 1900 items
+// on by XCD's rows, and through the queues, which level the heads' densities.  By
+// row against that, 8 / 8 heads 16000 tokens (2000 items): selected lists 304 /
+// 250 us, random ones 254 / 236, dense 669 / 562; 20000 328 / 275, 334 / 303, 1100 /
+// 851; 16 / 16 10000 (2512) 242 / 213, 321 / 298, 513 / 443; fewer items 16 / 16
+// 6000 (1504) 127 / 125, 150 / 166, 179 / 185; rows of 50 and 63 blocks, 40 / 8,
+// 86 / 124 and 116 / 141.  Past the cache line an XCD's own heads still pay, by
+// group against by XCD's rows: 8 / 8 49145 (192 MiB) 874 / 617, 699 / 686, 5841 /
+// 4770; not on random lists with two heads per XCD or much more memory: 16 / 16
+// 32000 (250 MiB) 912 / 787 selected but 1139 / 1204 random, 64000 1574 / 1405 and
+// 2393 / 2786; 8 / 8 128000 (500 MiB) random 2084 / 2154.  selected: the lists are
+// known to be a selection's.
+constexpr int kOwnHeadItems = 1900, kOwnHeadBlocks = 96;
+inline bool own_head_rows(int n_tokens, int n_q_heads, int n_kv_heads, int row_bytes, int block_size, int n_blocks,
+                          bool selected) {
+  return block_size == 64 && row_bytes > 256 && n_kv_heads % 8 == 0 && n_q_heads / n_kv_heads % 8 != 0 &&
+         n_blocks > kOwnHeadBlocks && n_blocks * n_q_heads > kOwnHeadItems &&
+         (int64_t)n_tokens * n_kv_heads * row_bytes <= (selected ? 512 : n_kv_heads == 8 ? 256 : 128) * (int64_t(1) << 20);
+}
+
+inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row_bytes, int block_size, int n_blocks,
+                            bool selected = false) {
+  if (own_head_rows(n_tokens, n_q_heads, n_kv_heads, row_bytes, block_size, n_blocks, selected)) return kByXcdRow;
   if (!row_major_work(n_tokens, n_kv_heads, row_bytes, block_size)) return kByGroup;
   const bool tiles = kv_heads_tile_xcds(n_kv_heads);
   const int few = row_bytes > 256 ? 3072 : tiles ? 4096 : 8192;
   if (block_size > 128 || n_blocks * n_q_heads <= few) return kByRow;
   return tiles ? kByXcdRow : kByGroup;
+}
+
+// Items past which a bf16 launch over one sequence goes through the queues
+// (launch_slots), where the GPU holds `resident` workgroups at once.  At B = 64
+// the queues cost some 20 us a launch and 1 us an item, which short rows do not
+// win back.  Queues against per slot: 64 / 8 heads 3593 tokens (57 blocks, 3648
+// items) selected lists 178 / 159, random ones 224 / 212, dense 257 / 247; 5000 (79)
+// 254 / 234, 381 / 379, 464 / 458; 6137 (96) 294 / 323, 504 / 522, 654 / 621.  With
+// one KV head every XCD has the same mix of rows and the queues only level their
+// ends: selected lists, 8 / 1 heads 27026 tokens 267 / 238, 49145 290 / 266, 114681
+// 443 / 425; random lists, 4 / 1 51200 481 / 525, 16 / 1 48000 1891 / 2023.
+inline int queue_line(int n_tokens, int n_q_heads, int n_kv_heads, int block_size, int n_blocks, int resident,
+                      bool selected) {
+  if (block_size != 64) return 3 * resident;
+  if (own_head_rows(n_tokens, n_q_heads, n_kv_heads, 512, block_size, n_blocks, selected)) return kOwnHeadItems;
+  if (selected && n_kv_heads == 1) return INT_MAX;
+  return n_blocks <= 80 ? 6 * resident : 3 * resident;
 }
 
 // The order of a launch over a batch: the longest rows of all sequences first

@@ -129,6 +129,21 @@ def test_queues_with_more_items_than_resident(B):
         _assert_same(_attend(shape, Q, K, V, counts, indices, ws), ref, f"eager call after replay {rep}")
 
 
+@pytest.mark.parametrize("heads,blocks", [((8, 8), 239), ((16, 16), 121)])
+def test_queues_of_launches_with_kv_heads_of_their_own_on_each_xcd(heads, blocks):
+    """B = 64 and a whole number of KV heads per XCD: queued from 1900 items on,
+    in the order that gives an XCD its own heads."""
+    import torch
+    w = WORKLOADS["tiny-2k"].with_(name="queue-own", seq_len=64 * blocks - 5, n_q_heads=heads[0], n_kv_heads=heads[1],
+                                   block_size=64, needles_per_kv_head=0, seed=70)
+    _say(f"[queue] {heads[0] * blocks} items, {heads[1]} KV heads")
+    shape, Q, K, V, counts, indices = _setup(w)
+    ws = torch.full((64,), -5, dtype=torch.int32, device="cuda")
+    _assert_same(_attend(shape, Q, K, V, counts, indices, None), _attend(shape, Q, K, V, counts, indices, ws),
+                 f"{heads}")
+    assert (ws != -5).all(), "the call did not take the queues"
+
+
 def test_caller_workspace_with_stale_contents_and_reuse():
     """A caller's workspace holding arbitrary values is reset by the call; the
     same workspace then serves a second, smaller problem."""

@@ -15,8 +15,11 @@ from paper_2609_20971_amd import build
 SOURCE = r"""
 #include "rbs_launch.hpp"
 using namespace rbs;
-extern "C" int choose(int n, int hq, int hkv, int row_bytes, int b, int M) {
-  return work_order(n, hq, hkv, row_bytes, b, M);
+extern "C" int choose(int n, int hq, int hkv, int row_bytes, int b, int M, int selected) {
+  return work_order(n, hq, hkv, row_bytes, b, M, selected != 0);
+}
+extern "C" int line(int n, int hq, int hkv, int b, int M, int resident, int selected) {
+  return queue_line(n, hq, hkv, b, M, resident, selected != 0);
 }
 extern "C" int choose_batch(int n, int hq, int hkv, int b, int blocks) { return batch_order(n, hq, hkv, b, blocks); }
 extern "C" int tokens_a_wave(int b, int blocks, int rows) { return row_tokens(b, blocks, rows); }
@@ -72,7 +75,7 @@ def test_a_launch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv, B, ro
     head at a time, or on n_kv / 8 of its own, whatever the head counts."""
     for n in (8100, 16384, 40000, 65536, 131072):
         M = -(-n // B)
-        order = lib.choose(n, hq, hkv, row_bytes, B, M)
+        order = lib.choose(n, hq, hkv, row_bytes, B, M, 0)
         assert order != BY_XCD_ROW or _tiles(hkv)
         if M * hq <= (3072 if row_bytes > 256 else 4096 if _tiles(hkv) else 8192):
             continue
@@ -83,6 +86,35 @@ def test_a_launch_of_many_items_keeps_an_xcd_to_few_kv_heads(lib, hq, hkv, B, ro
                 assert (np.diff(mine) >= 0).all()
             else:
                 assert len(np.unique(mine)) <= max(1, hkv // 8), (n, x, np.unique(mine))
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (16, 16), (24, 8), (32, 32)])
+@pytest.mark.parametrize("selected", [0, 1])
+def test_kv_heads_that_fill_the_xcds_stay_on_them_at_64_token_blocks(lib, hq, hkv, selected):
+    """From 1900 items of more than 96 blocks on, each XCD has KV heads of its own
+    (up to 128 MiB of K and V, 256 with eight heads, 512 for selected lists) and
+    the launch is queued."""
+    for blocks in (97, 120, 240, 312, 750, 1024, 2048):
+        n, items = 64 * blocks - 7, hq * blocks
+        if items <= 1900 or n * hkv * 512 > (512 if selected else 256 if hkv == 8 else 128) << 20:
+            continue
+        assert lib.choose(n, hq, hkv, 512, 64, blocks, selected) == BY_XCD_ROW
+        assert lib.line(n, hq, hkv, 64, blocks, 1024, selected) == 1900
+
+
+@pytest.mark.parametrize("hq,hkv,tokens,selected", [(8, 1, 27026, 1), (8, 1, 48000, 1), (16, 1, 16800, 1),
+                                                    (64, 8, 3300, 0), (64, 8, 5000, 1), (128, 8, 3000, 1)])
+def test_short_rows_and_one_kv_head_of_selected_lists_take_no_queue(lib, hq, hkv, tokens, selected):
+    blocks = -(-tokens // 64)
+    assert lib.line(tokens, hq, hkv, 64, blocks, 1024, selected) >= hq * blocks
+
+
+def test_the_general_line_is_three_times_the_resident_workgroups(lib):
+    for hq, hkv in HEADS:
+        for B, resident in ((128, 512), (256, 256)):
+            assert lib.line(20000, hq, hkv, B, -(-20000 // B), resident, 1) == 3 * resident
+    assert lib.line(8100, 32, 4, 64, 127, 1024, 0) == 3 * 1024
+    assert lib.line(48000, 8, 1, 64, 750, 1024, 0) == 3 * 1024
 
 
 @pytest.mark.parametrize("hq,hkv", HEADS)

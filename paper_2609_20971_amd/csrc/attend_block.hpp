@@ -564,8 +564,8 @@ hipError_t resident_grid(int threads, int* grid) {
 // line(resident), resident being what the device holds at once; otherwise one
 // workgroup per slot.  Few slots leave little to hand out, and the counter reset's
 // launch and the tickets are saved; with many, in-order dispatch holds slots back
-// where the rows' lengths differ.  The general line is three times the resident
-// workgroups.  Queues against per slot, 32 heads: 700 dense tokens (0.4
+// where the rows' lengths differ.  The line is general_line's or
+// queue_line's.  Queues against per slot, 32 heads: 700 dense tokens (0.4
 // times the resident slots) 25.7 / 19.9 us, 3001 (1.5 times) 99 / 89, 6000 (3
 // times) 299 / 288 dense and 251 / 251 on sparse lists, 8100 (4 times) 518 / 507
 // dense and 397 / 438 sparse; B = 64 6000 343 / 325 and 300 / 283, 8100 590 / 566

@@ -199,6 +199,9 @@ template <int BS>
 static hipError_t launch_attention_varlen_bs(const AttnCore& c, const AttnArgs& a, const SeqTable& t, hipStream_t s) {
   const int total = t.blk[t.n] * a.n_q_heads;
   const RowOrder rows = rows_by_length(t);
+  // (At B = 256 too, where one sequence takes the queues from twice the resident
+  // items on: a batch's rows are shorter, per slot / queues at 2.2 times, 28 / 4
+  // heads, three sequences 94 / 98 us, 64 / 8 four of 1 K tokens 46 / 48.)
   return launch_slots<attn_varlen_queue_kernel<BS>>(
       BS * 2, total, a.queue, s, [](int resident) { return 3 * resident; },
       [&](int grid) {

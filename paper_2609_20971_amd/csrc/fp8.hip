@@ -570,7 +570,7 @@ template <int BS>
 static hipError_t launch_attention_fp8_bs(const AttnF8Args& a, const int32_t* counts, const int32_t* indices,
                                           int* queue, hipStream_t s) {
   return launch_slots<attn_fp8_queue_kernel<BS>>(
-      BS * 2, a.M * a.Hq, queue, s, [](int resident) { return 3 * resident; },
+      BS * 2, a.M * a.Hq, queue, s, [](int resident) { return general_line(BS, resident); },
       [&](int grid) { hipLaunchKernelGGL(attn_fp8_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, counts, indices); },
       [&](int grid) { hipLaunchKernelGGL(attn_fp8_queue_kernel<BS>, dim3(grid), dim3(BS * 2), 0, s, a, counts, indices, queue); });
 }

@@ -268,9 +268,20 @@ inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row
   return tiles ? kByXcdRow : kByGroup;
 }
 
+// Items past which a launch goes through the queues (launch_slots), where the
+// GPU holds `resident` workgroups at once, at B = 128 and 256.  At B = 256 one
+// workgroup fills a compute unit and an item is long, so that the queues' own time
+// (some 10 us a launch) is won back earlier.  Queues / per slot at twice and at
+// three times the resident items: B = 256, 32 / 4 heads bf16 random lists 0.95 and
+// 0.85, selected 0.99 and 1.01, dense 1.00 and 1.01; FP8 0.91 and 0.82, dense 1.01
+// and 1.00; 8 / 1 bf16 0.97 and 0.94, 0.99 and 0.98, 0.93 and 0.99; at one and a
+// half times 1.05, 1.03, 1.03; B = 128 32 / 4 1.03 and 0.92, 1.03 and 0.99, 1.03 and
+// 1.03.
+inline int general_line(int block_size, int resident) { return (block_size > 128 ? 2 : 3) * resident; }
+
 // Items past which a bf16 launch over one sequence goes through the queues
-// (launch_slots), where the GPU holds `resident` workgroups at once.  At B = 64
-// the queues cost some 20 us a launch and 1 us an item, which short rows do not
+// (general_line past B = 64).  At B = 64 the queues cost some 20 us a launch and 1
+// us an item, which short rows do not
 // win back.  Queues against per slot: 64 / 8 heads 3593 tokens (57 blocks, 3648
 // items) selected lists 178 / 159, random ones 224 / 212, dense 257 / 247; 5000 (79)
 // 254 / 234, 381 / 379, 464 / 458; 6137 (96) 294 / 323, 504 / 522, 654 / 621.  With
@@ -279,7 +290,7 @@ inline WorkOrder work_order(int n_tokens, int n_q_heads, int n_kv_heads, int row
 // 443 / 425; random lists, 4 / 1 51200 481 / 525, 16 / 1 48000 1891 / 2023.
 inline int queue_line(int n_tokens, int n_q_heads, int n_kv_heads, int block_size, int n_blocks, int resident,
                       bool selected) {
-  if (block_size != 64) return 3 * resident;
+  if (block_size != 64) return general_line(block_size, resident);
   if (own_head_rows(n_tokens, n_q_heads, n_kv_heads, 512, block_size, n_blocks, selected)) return kOwnHeadItems;
   if (selected && n_kv_heads == 1) return INT_MAX;
   return n_blocks <= 80 ? 6 * resident : 3 * resident;

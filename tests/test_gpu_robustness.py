@@ -99,6 +99,7 @@ CASES = [
     dict(seq_len=1000, n_q_heads=4, n_kv_heads=4, block_size=64, seed=62),    # no GQA
     dict(seq_len=2900, n_q_heads=4, n_kv_heads=1, block_size=256, seed=63),   # two softmax steps per block
     dict(seq_len=100, n_q_heads=2, n_kv_heads=1, block_size=128, seed=64),    # N < B
+    dict(seq_len=128 * 99 - 5, n_q_heads=16, n_kv_heads=2, block_size=128, seed=66),  # 1584 items: work queues
 ]
 
 
@@ -137,19 +138,20 @@ def test_outputs_fully_written_and_nothing_past_them(case, workspace):
     _check_attention(obuf, lbuf)
 
 
-@pytest.mark.parametrize("workspace", [None, "auto"])
-def test_varlen_outputs_fully_written_and_nothing_past_them(workspace):
+@pytest.mark.parametrize("workspace,n_q_heads,seqs", [(None, 4, [700, 1536, 64, 2049, 1]),
+                                                      ("auto", 4, [700, 1536, 64, 2049, 1]),
+                                                      ("auto", 16, [700, 6100, 64, 2049, 1, 4300])])  # work queues
+def test_varlen_outputs_fully_written_and_nothing_past_them(workspace, n_q_heads, seqs):
     import torch
     import paper_2609_20971_amd as rbs
-    base = WORKLOADS["tiny-2k"].with_(name="robust-varlen", n_q_heads=4, n_kv_heads=2, block_size=128)
-    seqs = [700, 1536, 64, 2049, 1]
+    base = WORKLOADS["tiny-2k"].with_(name="robust-varlen", n_q_heads=n_q_heads, n_kv_heads=2, block_size=128)
     _say(f"[robust] varlen {seqs} workspace={workspace}")
     inputs = make_batch_inputs(batch_workloads(base, seqs, needles_per_2k=8))
     batch = rbs.Batch(seqs)
     shape = rbs.varlen_shape(batch, base.n_q_heads, base.n_kv_heads, base.block_size)
     Q, K, V = (H.to_device(inputs[x]) for x in ("q", "k", "v"))
     st = rbs.rbs_block_stats_varlen(shape, batch, K)
-    Mt, Ct, T, Hq = rbs.rbs_varlen_blocks(shape, batch), rbs.rbs_varlen_index_capacity(shape, batch), sum(seqs), 4
+    Mt, Ct, T, Hq = rbs.rbs_varlen_blocks(shape, batch), rbs.rbs_varlen_index_capacity(shape, batch), sum(seqs), n_q_heads
     cbuf = _buffer((Hq, Mt), torch.int32, POISON_COUNT, CANARY_I32)
     ibuf = _buffer((Hq, Ct), torch.int32, POISON_SLOT, CANARY_I32)
     rbs.rbs_select_varlen(shape, batch, Q, st, base.tau_base, base.tau_rescue, base.n_sink, base.n_local,

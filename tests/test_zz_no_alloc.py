@@ -2,7 +2,10 @@
 against rbs_sparse_prefill on the same inputs and lists, through the C ABI:
 two calls in a row on the library's static per-device scratch, the second on
 a smaller input (the counters left by the first call must not leak into it),
-O and LSE bit for bit; plus a graph-captured replay."""
+O and LSE bit for bit; plus a graph-captured replay.  The shapes have more
+items than the line past which a call goes through the work queues, whose
+counters the scratch holds (three times the workgroups that the GPU holds at
+once); a third call of few items runs without them."""
 
 from __future__ import annotations
 
@@ -35,6 +38,12 @@ def _case(w, tau=(0.9, 0.95)):
     return shape, Q, K, V, counts, indices, O_ref, lse_ref
 
 
+def _queued_tokens(n_q_heads):
+    """Tokens of a prompt with a few more items than the queues' line, B = 128."""
+    import torch
+    return 128 * (3 * 2 * torch.cuda.get_device_properties(0).multi_processor_count // n_q_heads + 3) - 5
+
+
 def _noalloc(case):
     import torch
     import paper_2609_20971_amd as rbs
@@ -48,17 +57,18 @@ def _noalloc(case):
 
 def test_noalloc_matches_the_workspace_entry_point_twice_second_smaller():
     import torch
-    big = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=8191, block_size=128, n_q_heads=8, n_kv_heads=2,
-                                     needles_per_kv_head=6, seed=41)
-    small = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=1000, block_size=64, n_q_heads=4, n_kv_heads=2,
+    big = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=_queued_tokens(16) + 1500, block_size=128, n_q_heads=16,
+                                     n_kv_heads=2, needles_per_kv_head=6, seed=41)
+    small = big.with_(seq_len=_queued_tokens(16), seed=44)
+    few = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=1000, block_size=64, n_q_heads=4, n_kv_heads=2,
                                        needles_per_kv_head=2, seed=42)
-    for w in (big, small):
+    cases = [(w, _case(w)) for w in (big, small, few)]  # (their own calls run before, not in between)
+    for w, case in cases:
         _say(f"[noalloc] N={w.seq_len} Hq={w.n_q_heads} Hkv={w.n_kv_heads} B={w.block_size}")
-        case = _case(w)
         O, lse = _noalloc(case)
         assert torch.equal(O.view(torch.int16), case[6].view(torch.int16))
         assert torch.equal(lse, case[7])
-    _say("[noalloc] two calls in a row (second smaller): O and LSE identical to rbs_sparse_prefill")
+    _say("[noalloc] three calls in a row (each smaller): O and LSE identical to rbs_sparse_prefill")
 
 
 def test_noalloc_graph_replay():
@@ -66,7 +76,8 @@ def test_noalloc_graph_replay():
     three times with eager calls in between; every replay bit-identical."""
     import torch
     import paper_2609_20971_amd as rbs
-    w = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=3000, needles_per_kv_head=4, seed=43)
+    w = WORKLOADS["tiny-2k"].with_(name="noalloc", seq_len=_queued_tokens(16), n_q_heads=16, n_kv_heads=2, block_size=128,
+                                   needles_per_kv_head=4, seed=43)
     shape, Q, K, V, counts, indices, O_ref, lse_ref = case = _case(w)
     O = torch.empty_like(Q)
     lse = torch.empty_like(lse_ref)

@@ -14,7 +14,6 @@
 namespace {
 
 constexpr int kMaxTokens = 262144;
-constexpr int kMaxBlocks = 4096;
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -53,7 +52,7 @@ int check_shape(const rbs_shape* s) {
   if (s->n_tokens < 1 || s->n_tokens > kMaxTokens) return RBS_ERR_SHAPE;
   if (s->n_q_heads < 1 || s->n_kv_heads < 1) return RBS_ERR_SHAPE;
   if (s->n_q_heads % s->n_kv_heads != 0) return RBS_ERR_SHAPE;
-  if (blocks_of(s) > kMaxBlocks) return RBS_ERR_SHAPE;
+  if (blocks_of(s) > rbs::kMaxBlocks) return RBS_ERR_SHAPE;
   if ((int64_t)s->n_q_heads * blocks_of(s) > INT32_MAX / 2) return RBS_ERR_SHAPE;
   rbs::Strides st;
   return strides_of(s, &st);
@@ -148,7 +147,7 @@ int check_batch(const rbs_shape* s, const rbs_batch* b, rbs::SeqTable* t) {
     const int64_t n = b->seq_tokens[q];
     if (n < 1 || n > kMaxTokens) return RBS_ERR_SHAPE;
     const int64_t m = (n + s->block_size - 1) / s->block_size;
-    if (m > kMaxBlocks) return RBS_ERR_SHAPE;
+    if (m > rbs::kMaxBlocks) return RBS_ERR_SHAPE;
     tok += n;
     blk += m;
     cap += m * (m + 1) / 2;

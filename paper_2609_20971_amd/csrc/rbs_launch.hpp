@@ -90,6 +90,7 @@ inline size_t summary_bytes(int n_kv_heads, int n_blocks) {
 // blocks blk[s] .. blk[s+1]-1 of the block arrays and index-list slots
 // cap[s] .. cap[s+1]-1 of every query head; a single sequence is {n = 1}.
 constexpr int kMaxSeqs = 64;
+constexpr int kMaxBlocks = 4096;  // key blocks of a sequence (api.hip refuses more)
 constexpr int kMaxDevices = 64;  // devices whose resident-grid size the launchers cache
 constexpr int kQueues = 8;       // work queues of a persistent attention launch, one per XCD
 constexpr int kQueueInts = 64;   // its workspace: 256 bytes, the eight counters spread over it

@@ -433,7 +433,8 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
   // L_res(b) = L_base(b).  The remaining blocks (a few percent) get their exact
   // rescue scores, 32 at a time as the listing finds them.
   float thr_base = mb + c.log2_tau_base, thr_res = -INFINITY;
-  // Per 64 blocks (lane k: blocks 64 k ..; M <= 4096), bit b % 64: selected by
+  static_assert(kMaxBlocks <= 64 * kWave, "one mask of 64 blocks per lane");
+  // Per 64 blocks (lane k: blocks 64 k ..), bit b % 64: selected by
   // the base branch; L[b] is the rescue score (no uplift, or a candidate).
   uint64_t in_base = 0, res_in_l = 0;
   if constexpr (MODE == kSelectFullL2) thr_res = mb + c.log2_tau_rescue;

@@ -17,9 +17,8 @@
 namespace rbs {
 
 constexpr int kStatsThreads = 256;
-constexpr int kMaxBlocks = 4096;  // T PER of the largest quantile_kernel
 
-// Maximum / minimum of x over the 64 lanes, in every lane.
+// Maximum of x over the 64 lanes, in every lane.
 __device__ __forceinline__ uint32_t wave_max_u(uint32_t x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -218,7 +217,7 @@ __global__ __launch_bounds__(kStatsThreads) void box_kernel(const uint16_t* __re
 // map onto kBins bins; the keys of each wanted rank's bin (a few) are listed by
 // their offset in it, and one wave per rank finds the value among them by bitwise
 // bisection with ballots (any number of keys, so any distribution).
-// Latency-bound, one workgroup per head: a chain of seven barriers (the 8-bit
+// Latency-bound, one workgroup per head: a chain of six barriers (the 8-bit
 // radix passes that it replaces took some twenty).  Kernel time at M = 32, 256,
 // 1024, 2048, 4096: 5.6, 7.0, 8.8, 12.2, 20.4 -> 5.0, 6.1, 6.1, 7.0, 7.6 us.
 constexpr int kBins = 1024;
@@ -422,6 +421,7 @@ hipError_t launch_stats_varlen(const StatsArgs& a, const SeqTable& t, hipStream_
 #undef RBS_STATS_CASE
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  static_assert(1024 * 4 >= kMaxBlocks, "the largest quantile kernel holds every radius of a head");
   int m_max = 0;
   for (int q = 0; q < t.n; ++q) m_max = t.blk[q + 1] - t.blk[q] > m_max ? t.blk[q + 1] - t.blk[q] : m_max;
   const dim3 heads(a.n_kv_heads, t.n);

@@ -1058,9 +1058,9 @@ def layer_sweep(args):
 # compiler flags); their joint hash identifies the kernel in the committed
 # rocprofv3 summaries.  The attention calls run the persistent (queue) kernels.
 KERNEL_SOURCES = {
-    "stats_kernel": ["stats.hip", "rbs_device.hpp", "../build.py"],
-    "quantile_kernel": ["stats.hip", "rbs_device.hpp", "../build.py"],
-    "select_kernel": ["select.hip", "rbs_device.hpp", "../build.py"],
+    "stats_kernel": ["stats.hip", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
+    "quantile_kernel": ["stats.hip", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
+    "select_kernel": ["select.hip", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
     "attn_queue_kernel": ["attn.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
     "attn_fp8_queue_kernel": ["fp8.hip", "attend_block.hpp", "rbs_device.hpp", "rbs_launch.hpp", "../build.py"],
 }

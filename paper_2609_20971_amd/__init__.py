@@ -4,7 +4,7 @@
     rbs_stats_summarize(shape, stats)   # select-ready summary from centroids/radii/beta held elsewhere
     counts, indices = rbs_select(shape, Q, stats, tau_b, tau_r, sink, local, recent)  # Sec. 3.2
     O = rbs_sparse_prefill(shape, Q, K, V, counts, indices)            # Sec. 3.3
-    counts, indices, O = rbs_select_attend(shape, Q, K, V, stats, ...)   # Sec. 3.2-3.3 in one pass
+    counts, indices, O = rbs_select_attend(shape, Q, K, V, stats, ...)   # Sec. 3.2-3.3 in one call
     box = rbs_block_box(shape, K); rbs_select_variant(shape, Q, stats, "box", rho, ..., box=box)  # supporting selectors
     batch = Batch([n0, n1, ...]); shape = varlen_shape(batch, H_q, H_kv, B)   # independent sequences, packed
     stats = rbs_block_stats_varlen(shape, batch, K); ...; rbs_sparse_prefill_varlen(shape, batch, Q, K, V, ...)

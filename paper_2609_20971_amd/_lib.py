@@ -530,7 +530,7 @@ def rbs_sparse_prefill_noalloc(shape: rbs_shape, Q, K, V, counts, indices, O, so
 def rbs_select_attend(shape: rbs_shape, Q, K, V, stats: BlockStats, tau_base: float, tau_rescue: float,
                       n_sink: int, n_local: int, n_recent: int, softmax_scale: float = 0.0, counts=None,
                       indices=None, O=None, lse=None, stream=None, workspace=AUTO):
-    """Stages 2 and 3 in one pass; returns (counts, indices, O) as the two calls would."""
+    """Stages 2 and 3 in one call; returns (counts, indices, O) as the two calls would."""
     qs = _check_q(shape, Q)
     kvs = _check_kv(shape, K, V)
     named = _check_stats(shape, stats, need_fp32=False)

@@ -486,8 +486,15 @@ struct QueueTicket {
   // Lane 0 of wave 0 takes a ticket.  (The other lanes adding zero instead of
   // standing aside made the compiler sum the wave's 64 addends in a scalar loop
   // first, ~1 us.)  Called as an item's last block begins, the atomic's round trip
-  // (~2.5 us across the XCDs) runs beside that block's work; called earlier, a
-  // workgroup would hold an item that others could run.
+  // (~2.5 us across the XCDs) runs beside that block's work: in the FP8 kernel all
+  // of it, in the bf16 kernel QK^T and the softmax only, whose wait for V counts
+  // the atomic too.  Called earlier, a workgroup would hold an item that others
+  // could run.
+  // A branch that only one lane takes, in a loop with barriers, has to stay free
+  // of barriers: a ticket loop written around `if (threadIdx.x == 0)` with the
+  // barrier inside was once compiled into a loop whose lanes met different
+  // numbers of barriers, and hung.  Here the branch holds the atomic alone, and
+  // every thread comes to it: `taken` and the block count that decide are uniform.
   __device__ __forceinline__ void take() {
     if (taken) return;
     taken = true;
@@ -502,8 +509,8 @@ struct QueueTicket {
 // past the end of its queue means the queue is empty (tickets only grow); the
 // wave then looks at all eight counters at once (lane l reads counter l % 8)
 // and goes on to the next queue with a slot left, so that the end of a launch
-// costs a workgroup two round trips and not one per queue (700 dense tokens, 32
-// heads, B = 128: 44.6 -> 25.7 us; 2048 tokens, 2 heads, B = 64: 67.4 -> 49.0
+// costs a workgroup two round trips and not one per queue (some 18 us of a launch:
+// 700 dense tokens, 32 heads, B = 128, which takes no queue any more, 44.6 -> 25.7
 // us).  Control flow around the barriers is uniform.
 __device__ __forceinline__ int next_slot(QueueTicket& k, int total, int* lds_slot) {
   for (;;) {

@@ -31,7 +31,9 @@ __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   attend_slot<BS>(c, counts, indices, capacity, blockIdx.x, gridDim.x, k_lds, v_lds, [] {});
 }
 
-// Persistent form: total = M * H_q work slots, queue = kQueueInts zeroed ints.
+// Persistent form: total = M * H_q work slots, queue as reset_queues leaves it.
+// (B = 256 takes all 256 VGPRs; two are spilled for an item's length and read back
+// once per item, none in the block loop.)
 template <int BS>
 __global__ __launch_bounds__(BS * 2) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_queue_kernel(
     AttnCore c, const int32_t* __restrict__ counts, const int32_t* __restrict__ indices, int64_t capacity,

@@ -22,9 +22,11 @@
 // to an ascending index list with wave ballots.
 //
 // What bounds it: per 32 centroids and 32 tokens 8 matrix ops (256 cycles of a
-// SIMD) and ~230 cycles of vector work (16 exponentials, their sums), which one
-// SIMD overlaps only in part (measured 420 cycles), and the read of Q (alone
-// 132 us of the 300 us at 48K tokens, 64 heads).  A row in one wave needs no
+// SIMD) and vector work of nearly that length (16 exponentials, their sums), which
+// one SIMD overlaps only in part, and the read of Q, which no tile's work covers
+// (0.8 GB at 48K tokens, 64 heads).  A wave of 128 tokens takes all 256 VGPRs and
+// spills 13 to 16 more, written as Q is read and read back on the way to the tile
+// loop: some 30 accesses per row, none in a loop.  A row in one wave needs no
 // barrier after the base pass, and one staged operand read serves up to 4
 // matrix ops.  Against one workgroup of B / 32 waves per row (32 tokens a
 // wave, every step behind a barrier), selection alone, 32 / 4 heads: B = 128

@@ -383,7 +383,10 @@ __device__ __forceinline__ void select_rows(const SelectCore& c, int g, int chun
   };
   bool plain_prev = false;
   for (int tile = 0; tile < n_tiles; ++tile) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's part of the tile, its uplifts and norms
+    // This wave's part of the tile, its uplifts and norms (vmcnt 0), and its pairs
+    // and scores in LDS (lgkmcnt 0: left to the barrier, the compiler drops that
+    // wait on the way round the loop, because another one stands right before it).
+    __builtin_amdgcn_s_waitcnt(0x0070);
     __syncthreads();                     // the tile is complete, and the other buffer free
     const float u = u_cur, cn = cn_cur;
     if (tile + 1 < n_tiles) {
